@@ -5,17 +5,18 @@
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhq.so")
-SOURCES = [os.path.join(CSRC, "hq_kernels.hip"), os.path.join(CSRC, "hq_host.cpp")]
+SOURCES = [os.path.join(CSRC, f) for f in ("hq_kernels.hip", "hq_gemm.hip", "hq_host.cpp")]
 DEPS = SOURCES + [os.path.join(CSRC, "hq_internal.h"), os.path.join(CSRC, "calib_table.inc"),
                   os.path.join(os.path.dirname(HERE), "include", "hq.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # every fp32 rounding in the kernels is the one written; no fused contractions
     "-ffp-contract=off",
     # no packed fp32 vector instructions (v_pk_*_f32) are generated
@@ -32,14 +33,28 @@ def stale() -> bool:
 
 
 def build(verbose: bool = False) -> str:
+    # one object per source, compiled side by side, then linked
     tmp = LIB + ".tmp"
-    cmd = [HIPCC] + FLAGS + ["-o", tmp] + SOURCES
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        sys.stderr.write(r.stdout + r.stderr)
-        raise RuntimeError("hipcc failed building libhq.so")
+    objs = [LIB + "." + os.path.basename(s) + ".o" for s in SOURCES]
+    cmds = [[HIPCC] + FLAGS + ["-c", "-o", o, s] for o, s in zip(objs, SOURCES)]
+    link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        if r.returncode != 0:
+            sys.stderr.write(r.stdout + r.stderr)
+            raise RuntimeError("hipcc failed building libhq.so")
+
+    try:
+        with ThreadPoolExecutor(len(cmds)) as pool:
+            list(pool.map(run, cmds))
+        run(link)
+    finally:
+        for o in objs:
+            if os.path.exists(o):
+                os.remove(o)
     os.replace(tmp, LIB)
     return LIB
 

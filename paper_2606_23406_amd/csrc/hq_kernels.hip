@@ -12,9 +12,7 @@
 // method writes as two roundings stays two roundings.  The fused
 // multiply-adds used below either have a multiplier of +-1 or +-2 (one
 // rounding of a sum or difference, the same as the add or subtract they
-// replace) or work on integer values (exact); the one exception is the int8
-// GEMM's per-tile rescale, a floating-point accumulation whose results are
-// held to a tolerance rather than bit for bit.
+// replace) or work on integer values (exact).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -3553,428 +3551,6 @@ __global__ __launch_bounds__(256) void hq_act_prep_kernel(hq_actprep_args A) {
 }
 
 
-// ------------------------------------------------------------ block-scaled GEMM
-// int8 and E4M3: out[m, n] = s_x[m] * sum_t g[n, t] * P_t[m, n], P_t the sum
-// over one factor tile of K: exact int32 on the int8 matrix cores
-// (v_mfma_i32_32x32x32_i8), fp32 on the f8f6f4 ones for E4M3
-// (v_mfma_scale_f32_32x32x64_f8f6f4 with unit scales).  MXFP4: out[m, n] =
-// sum_k X[m, k] W[n, k] over the element-times-block-scale values on the
-// same instruction, whose E8M0 scales carry every factor.
-// Workgroup tile 256 (tokens) x 128 (weight rows), eight waves in 4 x 2, each
-// 64 x 64 = 2 x 2 MFMA blocks, one workgroup per CU.  An LDS stage is 128
-// bytes of every A and B row (one K tile of int8 / E4M3, two of MXFP4) plus
-// its side data (tile factors, MX block scales), in a ring of three filled
-// straight from global memory by direct-to-LDS loads, with no register
-// staging: stage t + 2 streams in while stage t is multiplied, by eight
-// waves in two groups half a stage apart (gemm_body_pp).
-// LDS rows are 128 bytes with the 16-byte chunk c of row r at position
-// c ^ ((r / 2) % 8): a wave's 1 KB direct load fills rows 8q .. 8q + 7 (lane
-// l at row 8q + l / 8, position l % 8), and the 16 lanes of one LDS cycle
-// reading one chunk of 16 consecutive rows cover the 64 banks exactly once.
-// Both operands are K-contiguous rows and every lane reads the same k range
-// of A and B, so the contraction pairs identical k whatever order the
-// instruction assigns inside a step.  Output lane l of a 32 x 32 block holds
-// column l % 32 and rows 8 (r / 4) + 4 (l / 32) + r % 4.
-
-typedef int v4i_t __attribute__((ext_vector_type(4)));
-typedef int v8i_t __attribute__((ext_vector_type(8)));
-typedef int v16i_t __attribute__((ext_vector_type(16)));
-typedef float v16f_t __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef const __attribute__((address_space(1))) void gbl_void_t;
-
-constexpr int kGemmM = 256, kGemmN = 128;  // the loads below assume 256 x 128 and 8 waves
-constexpr int kGemmThreads = 512;           // 8 waves, 4 (m) x 2 (n)
-constexpr int kGemmNB = kGemmN / 64;        // 32 x 32 blocks per wave along n
-constexpr int kGemmStageA = kGemmM * 128, kGemmStageB = kGemmN * 128;
-// side data of a stage: for int8 and E4M3 the weight rows' factors of the
-// stage's factor tile (float n for weight row n0 + n); for MXFP4 the 8 scale
-// bytes of each A row and of each B row
-constexpr int kGemmSideG = 0, kGemmSideXs = 1024, kGemmSideWs = 3072;
-constexpr int kGemmStages = 3;  // LDS ring: stage t + 2 loads while stage t is multiplied
-template <int MODE> constexpr int gemm_stage_bytes() {
-  return kGemmStageA + kGemmStageB + (MODE == 2 ? 4096 : 512);
-}
-template <int MODE> constexpr int gemm_lds_bytes() { return kGemmStages * gemm_stage_bytes<MODE>(); }
-static_assert(gemm_lds_bytes<2>() <= 160 * 1024, "the LDS ring fits one CU");
-
-template <bool C, class T, class F> struct gemm_pick { using type = T; };
-template <class T, class F> struct gemm_pick<false, T, F> { using type = F; };
-template <int MODE> struct GemmMode {
-  static constexpr int U = MODE == 2 ? 2 : 1;  // 128-deep K units per stage
-  using acc_t = typename gemm_pick<MODE == 0, v16i_t, v16f_t>::type;
-};
-
-// The direct-to-LDS loads go through buffer resources based at the
-// workgroup's first A row, B row, factor row and scale rows: a lane's 32-bit
-// offset within them is fixed for the whole K loop and the stage's offset is
-// a scalar.  4 A and 2 B row groups per wave (16 bytes a lane, lane l at row
-// 8q + l / 8 and K chunk (l % 8) ^ ((4q + l / 16) % 8)), then the side data
-// (4 bytes a lane): for int8 and E4M3 factor dword j * 64 + l = g[n0 + 64 j +
-// l, t >> lm] with j = w % 2, for MXFP4 scale dword d = w * 64 + l of the A
-// rows and d = (w % 4) * 64 + l of the B rows (row d / 2, half d % 2).  Waves
-// with equal j (or w % 4) load the same values to the same place, so every
-// wave issues the same loads and the loop has no branch.  Rows past M or N
-// read the last valid row: they only feed outputs that are never stored,
-// and every access stays inside its resource.
-struct GemmLoads {
-  __amdgpu_buffer_rsrc_t ra, rb, rg, rxs, rws;
-  uint32_t a[4], b[2], g, xs, ws;
-  int lm;  // log2 of the 128-deep K units per factor tile
-};
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t gemm_rsrc(const void* base, int64_t bytes) {
-  // raw buffer (stride 0); the third descriptor word of gfx9 data buffers.
-  // The operands are workgroup-uniform: read them into scalar registers.
-  const uint64_t p = (uint64_t)base;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-  const int n = __builtin_amdgcn_readfirstlane((int)bytes);
-  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), (short)0, n, 0x00020000);
-}
-
-template <int MODE>
-__device__ __forceinline__ GemmLoads gemm_loads(const hq_gemm_args& A, int64_t m0, int64_t n0,
-                                                int wave, int lane) {
-  const int64_t rb = MODE == 2 ? A.K / 2 : A.K;  // row bytes
-  const int64_t T = A.K / A.tile, ks = A.K / 32;  // factors and MX scale bytes per row
-  const int64_t ma = min<int64_t>(A.M - m0, kGemmM), nb = min<int64_t>(A.N - n0, kGemmN);
-  GemmLoads L;
-  L.ra = gemm_rsrc(A.xq + m0 * rb, ma * rb);
-  L.rb = gemm_rsrc(A.w + n0 * rb, nb * rb);
-  L.rg = gemm_rsrc(MODE != 2 ? A.g + n0 * T : nullptr, MODE != 2 ? nb * T * 4 : 0);
-  L.rxs = gemm_rsrc(MODE == 2 ? A.xs + m0 * ks : nullptr, MODE == 2 ? ma * ks : 0);
-  L.rws = gemm_rsrc(MODE == 2 ? A.ws + n0 * ks : nullptr, MODE == 2 ? nb * ks : 0);
-  const int rr = lane >> 3;
-  // row 8q + rr holds chunk (lane % 8) ^ ((4q + lane / 16) % 8) at position lane % 8
-  auto kc = [&](int q) { return (uint32_t)(((lane & 7) ^ ((4 * q + (lane >> 4)) & 7)) << 4); };
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int q = wave * 4 + i;
-    L.a[i] = (uint32_t)(min<int64_t>(8 * q + rr, ma - 1) * rb) + kc(q);
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int q = wave * 2 + i;
-    L.b[i] = (uint32_t)(min<int64_t>(8 * q + rr, nb - 1) * rb) + kc(q);
-  }
-  L.lm = __builtin_ctz((uint32_t)(A.tile / HQ_TILE));
-  L.g = (uint32_t)(min<int64_t>((wave & 1) * 64 + lane, nb - 1) * T * 4);
-  const int d = wave * 64 + lane, e = (wave & 3) * 64 + lane;
-  L.xs = (uint32_t)(min<int64_t>(d >> 1, ma - 1) * ks + (d & 1) * 4);
-  L.ws = (uint32_t)(min<int64_t>(e >> 1, nb - 1) * ks + (e & 1) * 4);
-  return L;
-}
-
-// Direct-to-LDS loads of stage t into `stage` (wave is wave-uniform).
-template <int MODE>
-__device__ __forceinline__ void gemm_fetch(const GemmLoads& L, int64_t t, int wave, int8_t* stage) {
-  const uint32_t so = (uint32_t)(t * 128);
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(L.ra, (lds_void_t*)(stage + (wave * 4 + i) * 1024), 16,
-                                             L.a[i], so, 0, 0);
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(L.rb, (lds_void_t*)(stage + kGemmStageA + (wave * 2 + i) * 1024),
-                                             16, L.b[i], so, 0, 0);
-  int8_t* const side = stage + kGemmStageA + kGemmStageB;
-  if constexpr (MODE != 2) {
-    // the stage's factor tile; MXFP4 blocks carry the factors in their scales
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(L.rg, (lds_void_t*)(side + kGemmSideG + (wave & 1) * 256), 4,
-                                             L.g, (uint32_t)((t >> L.lm) * 4), 0, 0);
-  } else {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(L.rxs, (lds_void_t*)(side + kGemmSideXs + wave * 256), 4,
-                                             L.xs, (uint32_t)(t * 8), 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(L.rws, (lds_void_t*)(side + kGemmSideWs + (wave & 3) * 256),
-                                             4, L.ws, (uint32_t)(t * 8), 0, 0);
-  }
-}
-
-// 16 bytes of row `row`, K chunk c (0..7) of a stage operand
-__device__ __forceinline__ v4i_t gemm_frag(const int8_t* base, int row, int c) {
-  return *(const v4i_t*)(base + row * 128 + ((c ^ ((row >> 1) & 7)) << 4));
-}
-
-// MXFP4: a lane's scale words from the side data: the 8 scale bytes of its
-// row, shifted so that byte 0 / byte 2 of the low word are the lane's blocks
-// of the stage's first / second 64-deep step and those of the high word its
-// third / fourth (the lane's half of step s is block 2 s + l / 32).
-__device__ __forceinline__ uint2 mx_scales(const int8_t* side, int row, int lane) {
-  const uint2 w = *(const uint2*)(side + row * 8);
-  const uint32_t sh = 8u * (uint32_t)(lane >> 5);
-  return make_uint2(w.x >> sh, w.y >> sh);
-}
-
-template <int OPSEL>
-__device__ __forceinline__ v16f_t mfma_mxfp4(v4i_t a, v4i_t b, v16f_t c, uint32_t sa, uint32_t sb) {
-  const v8i_t a8 = {a[0], a[1], a[2], a[3], 0, 0, 0, 0};
-  const v8i_t b8 = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
-  // cbsz = blgp = 4: both operands E2M1; the scales are E8M0 bytes
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, c, 4, 4, OPSEL, (int)sa, OPSEL,
-                                                         (int)sb);
-}
-
-// A lane's factors for its kGemmNB weight columns (int8 and E4M3).
-__device__ __forceinline__ void gemm_side_g(const int8_t* side, int wn, int lane, float (&gv)[kGemmNB]) {
-#pragma unroll
-  for (int b = 0; b < kGemmNB; ++b)
-    gv[b] = ((const float*)(side + kGemmSideG))[wn * (kGemmN / 2) + b * 32 + (lane & 31)];
-}
-
-// Rescale elements [e0, e0 + E) of a finished tile's partials (block
-// j = e / 16 = 2 a + b, register r = e % 16) into the fp32 accumulators.
-template <int MODE, int E>
-__device__ __forceinline__ void gemm_rescale(int e0, const typename GemmMode<MODE>::acc_t (&p)[2][kGemmNB],
-                                             const float (&gv)[kGemmNB], float (&accf)[2][kGemmNB][16]) {
-#pragma unroll
-  for (int e = e0; e < e0 + E; ++e) {
-    const int j = e >> 4, r = e & 15, a = j / kGemmNB, b = j % kGemmNB;
-    accf[a][b][r] = __builtin_fmaf((float)p[a][b][r], gv[b], accf[a][b][r]);
-  }
-}
-
-// MFMA steps per stage: int8 32-deep (four), E4M3 64-deep (two), MXFP4
-// 64-deep over its two K units (four), and 16-byte chunks per fragment.
-template <int MODE> constexpr int gemm_pp_steps() { return MODE == 1 ? 2 : 4; }
-template <int MODE> constexpr int gemm_pp_fw() { return MODE == 1 ? 2 : 1; }
-
-// The MFMA phase of a stage: its steps into `cur`, from zero when FRESH (the
-// first stage of a factor tile, or of the whole product for MXFP4).
-template <int MODE, bool FRESH>
-__device__ __forceinline__ void gemm_mfma_pp(const v4i_t (&fa)[gemm_pp_steps<MODE>()][2][gemm_pp_fw<MODE>()],
-                                             const v4i_t (&fb)[gemm_pp_steps<MODE>()][kGemmNB][gemm_pp_fw<MODE>()],
-                                             const uint2 (&xs)[2], const uint2 (&ws)[kGemmNB],
-                                             typename GemmMode<MODE>::acc_t (&cur)[2][kGemmNB]) {
-  using acc_t = typename GemmMode<MODE>::acc_t;
-#pragma unroll
-  for (int s = 0; s < gemm_pp_steps<MODE>(); ++s)
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < kGemmNB; ++b) {
-        const acc_t c0 = (FRESH && s == 0) ? (acc_t){} : cur[a][b];
-        if constexpr (MODE == 0) {
-          cur[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[s][a][0], fb[s][b][0], c0, 0, 0, 0);
-        } else if constexpr (MODE == 1) {
-          const v8i_t x = {fa[s][a][0][0], fa[s][a][0][1], fa[s][a][0][2], fa[s][a][0][3],
-                           fa[s][a][1][0], fa[s][a][1][1], fa[s][a][1][2], fa[s][a][1][3]};
-          const v8i_t y = {fb[s][b][0][0], fb[s][b][0][1], fb[s][b][0][2], fb[s][b][0][3],
-                           fb[s][b][1][0], fb[s][b][1][1], fb[s][b][1][2], fb[s][b][1][3]};
-          // cbsz = blgp = 0: both operands E4M3; scale bytes 127 (2^0)
-          cur[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, c0, 0, 0, 0, 127, 0, 127);
-        } else {
-          // step s of the stage is K unit s / 2: its scale word, byte 2 (s % 2)
-          const uint32_t xa = s < 2 ? xs[a].x : xs[a].y, wb = s < 2 ? ws[b].x : ws[b].y;
-          cur[a][b] = (s & 1) ? mfma_mxfp4<2>(fa[s][a][0], fb[s][b][0], c0, xa, wb)
-                              : mfma_mxfp4<0>(fa[s][a][0], fb[s][b][0], c0, xa, wb);
-        }
-      }
-}
-
-// Output staging: a wave's 64 x 64 tile in LDS with rows of 64 values plus
-// 16 bytes of padding (rows 4 apart, written by the two lane halves, then
-// fall in different banks), 8 regions filling less than the stage ring.
-template <bool BF16> constexpr int gemm_out_row() { return BF16 ? 144 : 272; }
-constexpr int kGemmOutRegion = 64 * 272;
-static_assert(8 * kGemmOutRegion <= gemm_lds_bytes<0>(), "the output tiles fit the ring");
-
-// out rows r0 .. r0 + 63, columns c0 .. c0 + 63 of the wave's tile: each
-// value (s_x times the accumulator for int8 / E4M3; MXFP4's accumulator as
-// is) into LDS at its MFMA position, then 16-byte row pieces to global
-// memory (element stores at a ragged right edge).
-template <int MODE, bool BF16>
-__device__ __forceinline__ void gemm_store_tile(const hq_gemm_args& A, int8_t* tile,
-                                                const typename GemmMode<MODE>::acc_t (&cur)[2][kGemmNB],
-                                                const float (&accf)[2][kGemmNB][16], int64_t r0,
-                                                int64_t c0, int lane) {
-  constexpr bool RESCALE = MODE != 2;
-  constexpr int RS = gemm_out_row<BF16>();
-  constexpr int ES = BF16 ? 2 : 4;  // bytes per value
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      const int64_t m = r0 + row;
-      const float sxm = RESCALE && m < A.M ? A.sx[m] : 1.0f;
-#pragma unroll
-      for (int b = 0; b < kGemmNB; ++b) {
-        float v;
-        if constexpr (RESCALE)
-          v = sxm * accf[a][b][r];
-        else
-          v = cur[a][b][r];
-        int8_t* const p = tile + row * RS + (b * 32 + (lane & 31)) * ES;
-        if constexpr (BF16)
-          *(uint16_t*)p = (uint16_t)f32_to_bf16(v);
-        else
-          *(float*)p = v;
-      }
-    }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  constexpr int VPL = 16 / ES;            // values per 16-byte piece
-  constexpr int LPR = 64 / VPL;           // lanes per row
-  constexpr int ROWS = 64 / LPR;          // rows per pass
-#pragma unroll
-  for (int i = 0; i < 64 / ROWS; ++i) {
-    const int row = i * ROWS + lane / LPR, col = (lane % LPR) * VPL;
-    const int64_t m = r0 + row, n = c0 + col;
-    if (m >= A.M || n >= A.N) continue;
-    const uint4 v = *(const uint4*)(tile + row * RS + col * ES);
-    char* const dst = (char*)A.out + (m * A.N + n) * ES;
-    if (n + VPL <= A.N && ((m * A.N + n) * ES) % 16 == 0) {
-      *(uint4*)dst = v;
-    } else {
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int e = 0; e < VPL; ++e)
-        if (n + e < A.N) {
-          if constexpr (BF16)
-            ((uint16_t*)dst)[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-          else
-            ((uint32_t*)dst)[e] = w[e];
-        }
-    }
-  }
-}
-
-// The block-scaled GEMM, all three operand types: the eight waves in two
-// groups of four (waves 0-3 and 4-7: with a workgroup's waves placed on the
-// four SIMDs in turn, each SIMD holds one wave of each group; the results
-// do not depend on the placement) that run half a stage apart.  A wave's stage t has two phases: in V(t) it
-// issues the direct-to-LDS loads of stage t + 2, reads every fragment (and
-// for MXFP4 the block scale words) of stage t into registers and, for int8
-// and E4M3 when stage t starts a factor tile, rescales the previous tile's
-// partial sums into its fp32 accumulators; in M(t) it only issues MFMAs (a
-// long tile's stages accumulate into the same partials; MXFP4's scales
-// carry every factor, so its MFMAs accumulate the whole product).  Group 0
-// runs V(t) in phase 2t and M(t) in phase 2t + 1, group 1 one phase later,
-// and every phase ends at a workgroup barrier, so on each SIMD one wave's
-// MFMAs run while the other wave's LDS reads and rescale issue.  The barrier
-// waits leave only this wave's newest stage of loads in flight and no LDS
-// read outstanding: a stage is complete in LDS before either group reads
-// it, and its slot is refilled (stage t + 3, issued in phase 2t + 2) only
-// after group 1's reads of phase 2t + 1 have returned.  Every wave executes
-// the same 2 TS + 1 barriers: group 1 one before its first V phase, group 0
-// one after its last M phase.
-template <int MODE>
-__device__ __forceinline__ void gemm_body_pp(const hq_gemm_args& A) {
-  using acc_t = typename GemmMode<MODE>::acc_t;
-  constexpr bool RESCALE = MODE != 2;
-  constexpr int SB = gemm_stage_bytes<MODE>();
-  constexpr int NS = gemm_pp_steps<MODE>();
-  constexpr int FW = gemm_pp_fw<MODE>();
-  extern __shared__ __attribute__((aligned(16))) int8_t gsm[];
-  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
-  const int wsc = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, in a scalar register
-  const int wm = wsc >> 1, wn = wsc & 1, grp = wsc >> 2;
-  const int64_t m0 = (int64_t)blockIdx.y * kGemmM, n0 = (int64_t)blockIdx.x * kGemmN;
-  const int64_t TS = A.K / HQ_TILE / GemmMode<MODE>::U;  // LDS stages
-  const uint32_t tmask = (uint32_t)(A.tile / HQ_TILE) - 1u;  // stages per factor tile, less one
-
-  float accf[2][kGemmNB][16];
-  if constexpr (RESCALE) {
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < kGemmNB; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) accf[a][b][r] = 0.0f;
-  }
-  acc_t cur[2][kGemmNB];
-  float gcur[kGemmNB];
-  uint2 xs[2], ws[kGemmNB];
-  v4i_t fa[NS][2][FW], fb[NS][kGemmNB][FW];
-
-  const GemmLoads gl = gemm_loads<MODE>(A, m0, n0, wsc, lane);
-  constexpr int NL = MODE == 2 ? 8 : 7;  // buffer loads per wave and stage
-  gemm_fetch<MODE>(gl, 0, wsc, gsm);
-  gemm_fetch<MODE>(gl, min<int64_t>(1, TS - 1), wsc, gsm + SB);
-  // a phase boundary: the waits, the barrier, and no instruction scheduled
-  // across it (the MFMAs of M(t) would otherwise rise into V(t))
-  auto phase = [&]() {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NL) : "memory");
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  if (grp == 1) phase();  // group 1 starts one phase late
-  for (int64_t t = 0; t < TS; ++t) {
-    phase();
-    // V(t)
-    const int8_t* const stage = gsm + (t % 3) * SB;
-    const int8_t* const side = stage + kGemmStageA + kGemmStageB;
-    gemm_fetch<MODE>(gl, min(t + 2, TS - 1), wsc, gsm + ((t + 2) % 3) * SB);
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      // int8: 32-deep step, chunk 2 s + h; E4M3: 64-deep step, chunks 4 s + 2 h
-      // and the next; MXFP4: 64-deep step s of the stage, chunk 2 s + h (32
-      // E2M1 values, one MX block)
-#pragma unroll
-      for (int f = 0; f < FW; ++f) {
-        const int c = MODE == 1 ? 4 * s + 2 * h + f : 2 * s + h;
-#pragma unroll
-        for (int a = 0; a < 2; ++a) fa[s][a][f] = gemm_frag(stage, wm * 64 + a * 32 + (lane & 31), c);
-#pragma unroll
-        for (int b = 0; b < kGemmNB; ++b)
-          fb[s][b][f] = gemm_frag(stage + kGemmStageA, wn * (kGemmN / 2) + b * 32 + (lane & 31), c);
-      }
-    }
-    if constexpr (MODE == 2) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a) xs[a] = mx_scales(side + kGemmSideXs, wm * 64 + a * 32 + (lane & 31), lane);
-#pragma unroll
-      for (int b = 0; b < kGemmNB; ++b)
-        ws[b] = mx_scales(side + kGemmSideWs, wn * (kGemmN / 2) + b * 32 + (lane & 31), lane);
-    }
-    __builtin_amdgcn_sched_barrier(0);  // the reads issue first; the rescale runs under them
-    // int8 / E4M3: a factor tile of tmask + 1 stages accumulates into the
-    // partials, rescaled once, in the V phase that starts the next tile
-    const bool first = RESCALE ? ((uint32_t)t & tmask) == 0u : t == 0;  // wave-uniform
-    if constexpr (RESCALE) {
-      if (first) {
-        if (t > 0) gemm_rescale<MODE, 64>(0, cur, gcur, accf);
-        gemm_side_g(side, wn, lane, gcur);
-      }
-    }
-    phase();
-    // M(t)
-    if (first)
-      gemm_mfma_pp<MODE, true>(fa, fb, xs, ws, cur);
-    else
-      gemm_mfma_pp<MODE, false>(fa, fb, xs, ws, cur);
-  }
-  if (grp == 0) phase();  // the same barrier count in both groups
-  if constexpr (RESCALE) gemm_rescale<MODE, 64>(0, cur, gcur, accf);  // the last tile
-  // every wave's re-fetches of the last stage have landed: the ring is free
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-
-  // The wave's 64 x 64 outputs, staged in LDS (its own region of the ring)
-  // in the MFMA layout, then written out 16 bytes a lane along whole rows.
-  int8_t* const tile = gsm + wsc * kGemmOutRegion;
-  if (A.out_bf16)
-    gemm_store_tile<MODE, true>(A, tile, cur, accf, m0 + wm * 64, n0 + wn * 64, lane);
-  else
-    gemm_store_tile<MODE, false>(A, tile, cur, accf, m0 + wm * 64, n0 + wn * 64, lane);
-}
-
-__global__ __launch_bounds__(kGemmThreads, 1) void hq_gemm_i8_kernel(hq_gemm_args A) {
-  gemm_body_pp<0>(A);
-}
-
-__global__ __launch_bounds__(kGemmThreads, 1) void hq_gemm_f8_kernel(hq_gemm_args A) {
-  gemm_body_pp<1>(A);
-}
-
-__global__ __launch_bounds__(kGemmThreads, 1) void hq_gemm_mx4_kernel(hq_gemm_args A) {
-  gemm_body_pp<2>(A);
-}
-
-// ------------------------------------------------------------ utilities
-
 __global__ void hq_zero_kernel(uint32_t* p, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
@@ -4250,32 +3826,6 @@ int hq_launch_act_prep(const hq_actprep_args& a, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const size_t lds = (size_t)a.K * sizeof(float);
   hipLaunchKernelGGL(hq_act_prep_kernel, dim3((uint32_t)a.M), dim3(256), lds, st, a);
-  return (int)hipGetLastError();
-}
-
-int hq_launch_gemm(const hq_gemm_args& a, void* stream) {
-  if (a.K % 256 != 0) return -1;  // an even number of 128-deep K tiles
-  static bool lds_set = false;  // more than 64 KB of dynamic LDS needs an opt-in
-  if (!lds_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)hq_gemm_i8_kernel,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, gemm_lds_bytes<0>());
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)hq_gemm_f8_kernel,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, gemm_lds_bytes<1>());
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)hq_gemm_mx4_kernel,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, gemm_lds_bytes<2>());
-    if (e != hipSuccess) return (int)e;
-    lds_set = true;
-  }
-  const dim3 grid((uint32_t)((a.N + kGemmN - 1) / kGemmN), (uint32_t)((a.M + kGemmM - 1) / kGemmM));
-  hipStream_t st = (hipStream_t)stream;
-  if (a.fp8 == 2)
-    hipLaunchKernelGGL(hq_gemm_mx4_kernel, grid, dim3(kGemmThreads), gemm_lds_bytes<2>(), st, a);
-  else if (a.fp8)
-    hipLaunchKernelGGL(hq_gemm_f8_kernel, grid, dim3(kGemmThreads), gemm_lds_bytes<1>(), st, a);
-  else
-    hipLaunchKernelGGL(hq_gemm_i8_kernel, grid, dim3(kGemmThreads), gemm_lds_bytes<0>(), st, a);
   return (int)hipGetLastError();
 }
 
