@@ -176,9 +176,8 @@ def measured_traffic(kernel_key):
     """HBM bytes per launch of a codec kernel on this workload, from the
     rocprofv3 FETCH_SIZE / WRITE_SIZE summary in profiles/, if it was taken on
     the current kernel source (else None)."""
-    import hashlib
+    from paper_2606_23406_amd.build import source_sha256
     path = os.path.join(ROOT, "profiles", "codec_e8_4bps_llama8b_stack_hbm_traffic.txt")
-    src = os.path.join(ROOT, "paper_2606_23406_amd", "csrc", "hq_kernels.hip")
     if not os.path.exists(path):
         return None
     kv = {}
@@ -186,7 +185,7 @@ def measured_traffic(kernel_key):
         if "=" in line and not line.lstrip().startswith("#"):
             k, v = line.split("=", 1)
             kv[k.strip()] = v.strip()
-    if kv.get("source_sha256") != hashlib.sha256(open(src, "rb").read()).hexdigest():
+    if kv.get("source_sha256") != source_sha256():
         return None
     try:
         return float(kv[kernel_key + "_hbm_bytes_per_launch"])

@@ -2,6 +2,7 @@
 
     python -m paper_2606_23406_amd.build
 """
+import hashlib
 import os
 import subprocess
 import sys
@@ -10,8 +11,10 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhq.so")
-SOURCES = [os.path.join(CSRC, f) for f in ("hq_kernels.hip", "hq_gemm.hip", "hq_host.cpp")]
-DEPS = SOURCES + [os.path.join(CSRC, "hq_internal.h"), os.path.join(CSRC, "calib_table.inc"),
+SOURCES = [os.path.join(CSRC, f) for f in ("hq_encode.hip", "hq_decode.hip", "hq_fused.hip", "hq_gemm.hip",
+                                          "hq_host.cpp")]
+DEPS = SOURCES + [os.path.join(CSRC, "hq_internal.h"), os.path.join(CSRC, "hq_device.h"),
+                  os.path.join(CSRC, "calib_table.inc"),
                   os.path.join(os.path.dirname(HERE), "include", "hq.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -23,6 +26,14 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
+
+
+def source_sha256() -> str:
+    """Hash of the sources a library is built from (a measurement's stamp)."""
+    h = hashlib.sha256()
+    for d in sorted(DEPS):
+        h.update(open(d, "rb").read())
+    return h.hexdigest()
 
 
 def stale() -> bool:

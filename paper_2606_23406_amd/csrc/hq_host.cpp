@@ -1,6 +1,6 @@
 // Host side of libhq.so: plan construction, argument validation and the
 // C ABI declared in include/hq.h.  All codec arithmetic runs in the gfx950
-// kernels of hq_kernels.hip; this file derives constants and launches.
+// kernels of the .hip files; this file derives constants and launches.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -1,5 +1,5 @@
 // Internal declarations shared by the host plan (hq_host.cpp) and the gfx950
-// kernels (hq_kernels.hip) of libhq.so.  Not part of the public ABI.
+// kernels (.hip files) of libhq.so.  Not part of the public ABI.
 #pragma once
 
 #include <stddef.h>
@@ -193,7 +193,7 @@ struct hq_gemm_args {
   int32_t tile;       // RHT tile: the weight factors' K span (128 .. 2048)
 };
 
-// Kernel launchers (hq_kernels.hip); return a hipError_t as int.
+// Kernel launchers; return a hipError_t as int.
 int hq_launch_encode(const hq_plan_s* p, const hq_encode_args& a, const hq_rice_thr& t, int xt,
                      void* stream);
 int hq_launch_decode(const hq_plan_s* p, const hq_decode_args& a, int yt, void* stream);

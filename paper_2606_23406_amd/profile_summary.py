@@ -28,20 +28,20 @@ A SIMD issues at most one wave64 VALU instruction per ~2.5 cycles of the fast
 forms and ~4.3 of the slow ones (0.4 and 0.23 per cycle).
 """
 import csv
-import hashlib
 import json
 import os
 import sys
 from collections import defaultdict
 
+from paper_2606_23406_amd.build import source_sha256
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SRC = os.path.join(ROOT, "paper_2606_23406_amd", "csrc", "hq_kernels.hip")
 KERNELS = {
     "encode": "hq_encode_group_kernel<0, 0, false>",
     "decode": "hq_decode_group_kernel<0, 1, false>",
-    "gemm": "hq_gemm_i8_kernel",
-    "gemm_fp8": "hq_gemm_f8_kernel",
-    "gemm_mxfp4": "hq_gemm_mx4_kernel",
+    "gemm": "GemmCfg<0, 256, 256",
+    "gemm_fp8": "GemmCfg<1, 256, 256",
+    "gemm_mxfp4": "GemmCfg<2, 256, 256",
     "decode_gemv": "hq_decode_gemv_kernel",
     "decode_gemv_rows": "hq_decode_gemv_rows_kernel",
     "attention_keys": "hq_attn_kernel<0, 4, false>",
@@ -92,7 +92,7 @@ def traffic(fetch_csv, write_csv, log, out, cmd):
         "# FETCH_SIZE and WRITE_SIZE (KiB per dispatch, two rocprofv3 runs), each scaled by",
         "# 1 GiB / (the same counter on bench.py's 1 GiB device copy). Commands (repository root):",
     ] + [f"#   {c}" for c in cmd] + [
-        f"source_sha256 = {hashlib.sha256(open(SRC, 'rb').read()).hexdigest()}",
+        f"source_sha256 = {source_sha256()}",
         f"copy_dispatches = {len(cf)}",
         f"copy_fetch_kib = {sum(cf) / len(cf):.1f}",
         f"copy_write_kib = {sum(cw) / len(cw):.1f}",
