@@ -1,11 +1,88 @@
 // HyperQuant decode kernels for gfx950 (MI355X); the lane layout is in hq_device.h.
 #include <algorithm>
+#include <type_traits>
 
 #include "hq_device.h"
 
 #pragma clang fp contract(off)
 
 namespace {
+
+// ------------------------------------------------------------ transform on the matrix cores
+// A plain weight plan's codes are integers, so its inverse transform is exact
+// in any order, and 32 of a tile's 128 points fit one matrix-core step: with
+// lane l holding block (l & 3) | (l >> 4) << 2 of tile (l >> 2) & 3, the lane's 8
+// coordinates and the lanes l, l + 16, l + 32, l + 48 make the K index
+// 8 (l / 16) + j of v_mfma_f32_16x16x32_f16's B operand, column l % 16.  The A
+// operand is H32 with its rows in the order that returns every sum to the
+// lane layout it came from (row 4 g' + r of product h is coordinate 4 h + r
+// of lane group g'), and the blocks' two low index bits remain, as two DPP
+// butterflies.  The codes enter as 1536 + c in fp16 (exact for |c| < 512: one
+// shift-and-add per pair); the bias shows only in the all-ones row, where the
+// C operand takes 32 * 1536 away.  All values are integers below 2^24: exact.
+// Against the seven-stage transform on the VALU (integer conversions, 24 adds,
+// 32 cross-lane multiply-adds) it leaves 16 cross-lane ones.
+typedef _Float16 v8h_t __attribute__((ext_vector_type(8)));
+typedef float v4f_t __attribute__((ext_vector_type(4)));
+typedef uint32_t v4u_t __attribute__((ext_vector_type(4)));
+constexpr uint32_t kCodeBias = 0x66006600u;  // 1536 in each fp16 half
+
+struct MfmaRht {
+  v4u_t a0, a1;  // the two products' A rows, fp16 +-1 pairs
+  v4f_t c0;      // C of product 0
+  float f[2];    // stage signs of the lane's block bits 0 and 1
+  uint32_t sigma;
+  __device__ __forceinline__ explicit MfmaRht(int lane) {
+    const uint32_t r = lane & 3, go = (lane >> 2) & 3, gi = (uint32_t)lane >> 4;
+    const uint32_t s = __popc(gi & go) & 1u;
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      // K values j = 2 i and 2 i + 1: sign (-1)^(popc(j & r) + s)
+      const uint32_t lo = (__popc((2 * i) & r) + s) & 1u, hi = (__popc((2 * i + 1) & r) + s) & 1u;
+      w[i] = 0x3C003C00u ^ (lo << 15) ^ (hi << 31);
+    }
+    a0 = (v4u_t){w[0], w[1], w[2], w[3]};
+    a1 = (v4u_t){w[0], w[1], w[2] ^ 0x80008000u, w[3] ^ 0x80008000u};  // coordinate bit 2 set
+    c0 = (v4f_t){lane < 16 ? -32.0f * 1536.0f : 0.0f, 0.0f, 0.0f, 0.0f};
+    f[0] = (lane & 1) ? -1.0f : 1.0f;
+    f[1] = (lane & 2) ? -1.0f : 1.0f;
+    sigma = (uint32_t)(__popc((uint32_t)lane & 3u) & 1) << 31;
+    // kept in registers for the whole kernel
+    asm volatile("" : "+v"(a0), "+v"(a1), "+v"(c0), "+v"(f[0]), "+v"(f[1]), "+v"(sigma));
+  }
+  // y = sigma * (H c) for |c| < 512, c given as biased fp16 pairs.
+  __device__ __forceinline__ void small(const uint32_t (&pair)[4], float* y) const {
+    const v8h_t b = __builtin_bit_cast(v8h_t, (v4u_t){pair[0], pair[1], pair[2], pair[3]});
+    const v4f_t lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h_t, a0), b, c0, 0, 0, 0);
+    const v4f_t hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h_t, a1), b, (v4f_t){}, 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      y[j] = lo[j];
+      y[4 + j] = hi[j];
+    }
+    stages(y);
+  }
+  // The same for any code, on the VALU.
+  __device__ __forceinline__ void any(float* y, int lane) const {
+    fwht8_inlane(y);
+    const float s4 = (lane & 16) ? -1.0f : 1.0f, s5 = (lane & 32) ? -1.0f : 1.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) y[j] = __builtin_fmaf(y[j], s4, swz_xor16(y[j]));
+#pragma unroll
+    for (int j = 0; j < 8; ++j) y[j] = __builtin_fmaf(y[j], s5, lane_xor32(y[j]));
+    stages(y);
+  }
+  __device__ __forceinline__ void stages(float* y) const {
+    HQ_FMAC_DPP8("quad_perm:[1,0,3,2]", y, f[0]);
+    HQ_FMAC_DPP8("quad_perm:[2,3,0,1]", y, f[1]);
+  }
+};
+
+// 16 output bytes that this kernel does not read again.
+__device__ __forceinline__ void store_stream(void* p, uint4 v) {
+  __builtin_nontemporal_store((v4u_t){v.x, v.y, v.z, v.w}, (v4u_t*)p);
+}
 
 // SPW consecutive sub-streams per wave: 4, or 1 for launches too small to
 // fill the chip with four per wave.
@@ -28,7 +105,7 @@ __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_
   if (use_qjl)
     for (int i = tid; i < HQ_TILE * HQ_TILE / 4; i += 256)
       ((float4*)qmat)[i] = ((const float4*)A.qjl)[i];
-  s_sel[tid] = byte_select_entry((uint32_t)tid);  // 256 threads, one entry each
+  s_sel[tid] = kByteSelect.e[tid];  // 256 threads, one entry each
   __syncthreads();
 
   // this wave's sub-streams: SPW consecutive ones; their table entries are
@@ -45,12 +122,17 @@ __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_
   }
   DecHead head = dec_head<LAT>(A, sub0 < nsub, off[0], off[1], kbs[0], lane);
   const uint32_t spr = (uint32_t)A.spr;
-  const TwSigns sg(lane);
+  // plain weight plans transform their integer codes on the matrix cores, in
+  // that layout's lane order; group grp is block grp % 16 of tile grp / 16
+  constexpr bool PI = MODE <= 1 && !KV && LAT != kA2;
+  const uint32_t ltile = PI ? (uint32_t)(lane >> 2) & 3u : (uint32_t)lane >> 4;
+  const uint32_t grp = PI ? ltile * 16u + ((uint32_t)(lane & 3) | (uint32_t)(lane >> 4) << 2) : (uint32_t)lane;
+  const typename std::conditional<PI, MfmaRht, TwSigns>::type sg(lane);
   const uint32_t sbits = use_rot ? sign_bits8(A.smask, (lane & 15) * 8) : 0u;
   // tile factors g = r_s / (alpha n), once for the wave's tiles: lane l
-  // takes sub-stream l & 3 (SPW = 4) or the one sub-stream, and tile l >> 4
-  // (rows are contiguous, 4 tiles per sub-stream); with four, sub-stream i
-  // reads them back by a quad broadcast
+  // takes sub-stream l & 3 (SPW = 4) or the one sub-stream, and its tile
+  // (rows are contiguous, 4 tiles per sub-stream; a quad shares its tile);
+  // with four, sub-stream i reads them back by a quad broadcast
   static_assert(SPW == 4 || SPW == 1, "one sub-stream per lane of a quad, or one per wave");
   float gm = 0.0f;
   {
@@ -61,12 +143,13 @@ __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_
       const int64_t t =
           MODE >= 2 ? A.first_row * A.tpr + (int64_t)((((uint64_t)subq << 9) + (uint64_t)((lane >> 4) << 7)) >>
                                                        __builtin_ctz((uint32_t)A.tile))
-                    : A.first_row * A.tpr + 4 * (int64_t)subq + (lane >> 4);
+                    : A.first_row * A.tpr + 4 * (int64_t)subq + ltile;
       const float rs = fp16_norm ? (float)((const _Float16*)A.norms)[t] : ((const float*)A.norms)[t];
       gm = rs / A.alpha_n;
     }
   }
 
+  uint32_t lrow = sub0 / spr, csub = sub0 - lrow * spr;  // row and sub-stream in it, advanced below
 #pragma unroll
   for (int i = 0; i < SPW; ++i) {
     const uint32_t sub = sub0 + (uint32_t)i;
@@ -74,16 +157,15 @@ __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_
     DecHead next;
     if (i + 1 < SPW)
       next = dec_head<LAT>(A, sub + 1 < nsub, off[i + 1], off[i + 2], kbs[i + 1], lane);
-    const uint32_t lrow = sub / spr;
-    const uint32_t col = (sub - lrow * spr) * HQ_SUB + 8u * (uint32_t)lane;
+    const uint32_t col = csub * HQ_SUB + 8u * grp;
     const int64_t grow = A.first_row + lrow;
     // output signs, loaded before the bit walk
     uint4 sw = make_uint4(0u, 0u, 0u, 0u);
     if (MODE == 1) sw = *(const uint4*)(A.dsign16 + (col >> 1));
 
     uint32_t sym[8];
-    const bool ok = decode_symbols<LAT>(A, head, lane, buf, starts, s_sel, sym);
-    const unsigned long long bad = __ballot(!ok);  // wave-uniform
+    bool small;
+    const unsigned long long bad = decode_symbols<LAT>(A, head, lane, grp, buf, starts, s_sel, sym, small);
     if (bad && A.stats) {
       // count the sub-stream once (its first failing lane reports)
       if ((unsigned)lane == (unsigned)__builtin_ctzll(bad)) {
@@ -99,15 +181,21 @@ __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_
     if (bad) g = 0.0f;  // a corrupt sub-stream decodes as zeros, dither included
 
     if constexpr (MODE == 2) {
-      uint32_t packed[2] = {0u, 0u};
       uint32_t clamps = 0;
+      const int32_t hi = max(max(max(c[0], c[1]), max(c[2], c[3])), max(max(c[4], c[5]), max(c[6], c[7])));
+      const int32_t lo = min(min(min(c[0], c[1]), min(c[2], c[3])), min(min(c[4], c[5]), min(c[6], c[7])));
+      if (__ballot(hi > 127 || lo < -127) != 0ull) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        int32_t v = c[j];
-        if (v > 127) { v = 127; ++clamps; }
-        if (v < -127) { v = -127; ++clamps; }
-        packed[j >> 2] |= ((uint32_t)v & 0xFFu) << (8 * (j & 3));
+        for (int j = 0; j < 8; ++j) {
+          clamps += c[j] > 127 || c[j] < -127;
+          c[j] = max(min(c[j], 127), -127);
+        }
       }
+      uint32_t packed[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)  // the low bytes of four codes
+        packed[j] = __builtin_amdgcn_perm((uint32_t)c[4 * j + 1], (uint32_t)c[4 * j], 0x0C0C0400u) |
+                    __builtin_amdgcn_perm((uint32_t)c[4 * j + 3], (uint32_t)c[4 * j + 2], 0x04000C0Cu);
       int8_t* out = (int8_t*)A.y + (int64_t)lrow * A.ld + col;
       *(uint2*)out = make_uint2(packed[0], packed[1]);
       if ((col & (uint32_t)(A.tile - 1)) == 0)
@@ -128,10 +216,10 @@ __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_
       am = __builtin_fmaxf(am, dpp_xor<1>(am));
       am = __builtin_fmaxf(am, dpp_xor<2>(am));
       const int32_t X = mx_exponent(am);
-      const float inv = __builtin_ldexpf(1.0f, -X);  // exact: v / 2^X is exact
-      uint32_t packed = 0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) packed |= e2m1_code(v[j] * inv) << (4 * j);
+      uint32_t packed = e2m1_pair<0>(0u, v[0], v[1], X);
+      packed = e2m1_pair<1>(packed, v[2], v[3], X);
+      packed = e2m1_pair<2>(packed, v[4], v[5], X);
+      packed = e2m1_pair<3>(packed, v[6], v[7], X);
       uint8_t* out = (uint8_t*)A.y + (int64_t)lrow * A.ld + (col >> 1);
       *(uint32_t*)out = packed;
       if ((lane & 3) == 0) A.mxs[(int64_t)lrow * (A.spr * (HQ_SUB / 32)) + (col >> 5)] = (uint8_t)(X + 127);
@@ -157,6 +245,19 @@ __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_
       // transform exact in fp32 (|sum| <= 128 * 65536 < 2^24) whenever there
       // is no dither
       float y[8];
+      if constexpr (PI) {
+        if (small) {
+          uint32_t pair[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            pair[j] = ((uint32_t)c[2 * j + 1] << 16) + ((uint32_t)c[2 * j] + kCodeBias);
+          sg.small(pair, y);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) y[j] = (float)c[j];
+          sg.any(y, lane);
+        }
+      } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) y[j] = code_coord<LAT>(c[j], j);
       if (use_dither) {
@@ -171,6 +272,7 @@ __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_
       }
       if (use_qjl) qjl_tile(qmat, qstage, lane, y);  // y <- S^T y
       fwht128_tw(y, sg);
+      }
       const float g_tw = xor_sign(g, sg.sigma);
 #pragma unroll
       for (int j = 0; j < 8; ++j) y[j] = y[j] * g_tw;
@@ -187,10 +289,14 @@ __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_
         o.y = cvt_pk_bf16(y[2], y[3]) ^ sw.y;
         o.z = cvt_pk_bf16(y[4], y[5]) ^ sw.z;
         o.w = cvt_pk_bf16(y[6], y[7]) ^ sw.w;
-        *(uint4*)((uint16_t*)A.y + (int64_t)lrow * A.ld + col) = o;
+        store_stream((uint16_t*)A.y + (int64_t)lrow * A.ld + col, o);
       }
     }
     if (i + 1 < SPW) head = next;
+    if (++csub == spr) {
+      csub = 0;
+      ++lrow;
+    }
   }
 }
 
@@ -285,7 +391,7 @@ __device__ __forceinline__ void decode_wg_tiled(const hq_decode_args& A, const u
   const uint32_t wave = readfirst((uint32_t)(tid >> 6));
   uint32_t* buf = smem + wave * (A.lds_words + 66);
   uint32_t* starts = buf + A.lds_words + 2;
-  s_sel[tid] = byte_select_entry((uint32_t)tid);  // 256 threads, one entry each
+  s_sel[tid] = kByteSelect.e[tid];  // 256 threads, one entry each
   __syncthreads();
 
   const uint32_t n = (uint32_t)A.tile;
@@ -364,8 +470,9 @@ __device__ __forceinline__ void decode_wg_tiled(const hq_decode_args& A, const u
       next = dec_head<LAT>(A, sub + 1 < nsub, off[i + 1], off[i + 2], kbs[i + 1], lane);
     if (sub < nsub) {
       uint32_t sym[8];
-      const bool ok = decode_symbols<LAT>(A, head, lane, buf, starts, s_sel, sym);
-      const unsigned long long bad = __ballot(!ok);
+      bool small;
+      const unsigned long long bad =
+          decode_symbols<LAT>(A, head, lane, (uint32_t)lane, buf, starts, s_sel, sym, small);
       if (bad && A.stats && (unsigned)lane == (unsigned)__builtin_ctzll(bad)) {
         atomicAdd(&A.stats->corrupt_substreams, 1u);
         atomicCAS(&A.stats->status, 0u, (uint32_t)HQ_ERR_CORRUPT);
@@ -449,7 +556,7 @@ __global__ __launch_bounds__(256) void hq_decode_qjl_kernel(hq_decode_args A) {
   uint32_t* buf = smem + wave * (A.lds_words + 66);
   uint32_t* starts = buf + A.lds_words + 2;
   float* const Y = (float*)(smem + HQ_WAVES_PER_WG * (A.lds_words + 66));
-  s_sel[tid] = byte_select_entry((uint32_t)tid);
+  s_sel[tid] = kByteSelect.e[tid];
   // B operands: step s covers k = 4 s .. 4 s + 3 (lane / 16 picks k), block
   // cb the columns n = 32 wave + 16 cb + lane % 16
   float sb[32][2];
@@ -481,8 +588,9 @@ __global__ __launch_bounds__(256) void hq_decode_qjl_kernel(hq_decode_args A) {
       const uint32_t lrow = sub / spr;
       const uint32_t col = (sub - lrow * spr) * HQ_SUB + 8u * (uint32_t)lane;
       uint32_t sym[8];
-      const bool ok = decode_symbols<LAT>(A, head, lane, buf, starts, s_sel, sym);
-      const unsigned long long bad = __ballot(!ok);
+      bool small;
+      const unsigned long long bad =
+          decode_symbols<LAT>(A, head, lane, (uint32_t)lane, buf, starts, s_sel, sym, small);
       if (bad && A.stats && (unsigned)lane == (unsigned)__builtin_ctzll(bad)) {
         atomicAdd(&A.stats->corrupt_substreams, 1u);
         atomicCAS(&A.stats->status, 0u, (uint32_t)HQ_ERR_CORRUPT);

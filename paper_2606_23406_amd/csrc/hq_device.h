@@ -148,20 +148,7 @@ __device__ __forceinline__ int32_t unzigzag(uint32_t m) {
 
 // In-byte select table: entry v packs, 4 bits per rank k = 0..7, the position
 // of the k-th set bit of the byte value v (entries for ranks past popc(v)
-// are unused).
-__device__ __forceinline__ uint32_t byte_select_entry(uint32_t v) {
-  uint32_t e = 0, k = 0;
-#pragma unroll
-  for (uint32_t b = 0; b < 8; ++b) {
-    if ((v >> b) & 1u) {
-      e |= b << (4 * k);
-      ++k;
-    }
-  }
-  return e;
-}
-
-// The whole table, built at compile time; kernels copy it into LDS.
+// are unused); built at compile time, kernels copy it into LDS.
 struct ByteSelectTable {
   uint32_t e[256];
   constexpr ByteSelectTable() : e() {
@@ -177,16 +164,6 @@ struct ByteSelectTable {
   }
 };
 __constant__ ByteSelectTable kByteSelect = ByteSelectTable();
-
-// Position (0..31) of the r-th set bit (r from 0, r < popc(w)) of w: the
-// byte from cumulative byte popcounts, the bit from the table.
-__device__ __forceinline__ uint32_t select32_lut(uint32_t w, uint32_t r, const uint32_t* tbl) {
-  const uint32_t c1 = __popc(w & 0xFFu), c2 = __popc(w & 0xFFFFu), c3 = __popc(w & 0xFFFFFFu);
-  const uint32_t b = (uint32_t)(r >= c1) + (uint32_t)(r >= c2) + (uint32_t)(r >= c3);
-  const uint32_t below = b == 0 ? 0u : (b == 1 ? c1 : (b == 2 ? c2 : c3));
-  const uint32_t byte = __builtin_amdgcn_ubfe(w, 8 * b, 8);
-  return 8 * b + __builtin_amdgcn_ubfe(tbl[byte], 4 * (r - below), 3);
-}
 
 // Position (0..31) of the r-th set bit (r from 0) of w.
 __device__ __forceinline__ uint32_t select32(uint32_t w, uint32_t r) {
@@ -610,16 +587,15 @@ __device__ __forceinline__ uint32_t e4m3x4(float a, float b, float c, float d) {
   return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(c, d, lo, true);
 }
 
-// OCP FP4 E2M1 code of v (magnitudes 0, .5, 1, 1.5, 2, 3, 4, 6 as codes 0 .. 7):
-// the nearest value, ties to the even code, saturating at 6, the sign bit
-// (bit 3) kept also when v rounds to zero.  The comparisons place each tie
-// on its even side.
-__device__ __forceinline__ uint32_t e2m1_code(float v) {
-  const float a = __builtin_fabsf(v);
-  const uint32_t c = (uint32_t)(a > 0.25f) + (uint32_t)(a >= 0.75f) + (uint32_t)(a > 1.25f) +
-                     (uint32_t)(a >= 1.75f) + (uint32_t)(a > 2.5f) + (uint32_t)(a >= 3.5f) +
-                     (uint32_t)(a > 5.0f);
-  return c | ((__float_as_uint(v) >> 28) & 8u);
+// Two values as OCP FP4 E2M1 codes of v / 2^X (magnitudes 0, .5, 1, 1.5, 2, 3,
+// 4, 6 as codes 0 .. 7 with the sign in bit 3) in byte SEL of r, the first in
+// the low nibble: the nearest value, ties to the even code, saturating at 6,
+// the sign kept also when a value rounds to zero.  The instruction's scale
+// operand is the float 2^X, of which it takes the exponent field (0 for the
+// block exponent -127).
+template <int SEL>
+__device__ __forceinline__ uint32_t e2m1_pair(uint32_t r, float a, float b, int32_t X) {
+  return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, a, b, __uint_as_float((uint32_t)(X + 127) << 23), SEL);
 }
 
 // The MX block exponent X = floor(log2 amax) - 2 of a block whose largest
@@ -1094,81 +1070,60 @@ __device__ __forceinline__ DecHead dec_head(const hq_decode_args& A, bool active
   h.R = 64 * lane_rem_bits<LAT>(k0, k1);
   h.ok = active && end >= start && (int64_t)end <= A.cap_words && h.W <= A.lds_words &&
          k0 <= HQ_KMAX && h.R <= 32u * h.W;
-  const uint32_t Wl = h.ok ? h.W : 0u;
-  h.w0 = (uint32_t)lane < Wl ? A.payload[(uint64_t)start + lane] : 0u;
-  h.w1 = (uint32_t)lane + 64u < Wl ? A.payload[(uint64_t)start + 64u + lane] : 0u;
+  // a raw buffer of the sub-stream's words: lanes past its end read zero, with
+  // no per-lane branch
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(A.payload + start), (short)0, h.ok ? (int)(4u * h.W) : 0, 0x00020000);
+  h.w0 = __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, 0, 0);
+  h.w1 = __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4 + 256, 0, 0);
   return h;
 }
 
+// Position (0..31) of the r-th set bit (r from 0, r < popc(w)) of w: the byte
+// by halving, the bit from the table.
+__device__ __forceinline__ uint32_t select32_half(uint32_t w, uint32_t r, const uint32_t* tbl) {
+  const uint32_t c = __popc(w & 0xFFFFu);
+  const bool hi = r >= c;
+  const uint32_t v = hi ? w >> 16 : w & 0xFFFFu;
+  r = hi ? r - c : r;
+  const uint32_t c8 = __popc(v & 0xFFu);
+  const bool up = r >= c8;
+  const uint32_t byte = up ? v >> 8 : v & 0xFFu;
+  r = up ? r - c8 : r;
+  return (hi ? 16u : 0u) + (up ? 8u : 0u) + __builtin_amdgcn_ubfe(tbl[byte & 0xFFu], 4 * r, 3);
+}
+
+// decode_symbols' general path, for group `grp` of a sub-stream of Wl words
+// already in `buf`: any code length, corrupt sub-streams too.  A corrupt
+// sub-stream (any lane's parse failed) decodes as all-zero symbols in every
+// lane; callers drop its factor too.
 template <int LAT>
-__device__ __forceinline__ bool decode_symbols(const hq_decode_args& A, const DecHead& h, int lane,
-                                               uint32_t* buf, uint32_t* starts,
-                                               const uint32_t* seltbl, uint32_t* sym) {
-  const uint32_t kb = h.kb;
-  const uint32_t k0 = (LAT == kA2) ? (kb & 15u) : kb;
-  const uint32_t k1 = (LAT == kA2) ? (kb >> 4) : (LAT == kD4 ? (k0 > 0 ? k0 - 1 : 0) : k0);
+__device__ __forceinline__ bool decode_symbols_general(bool ok, uint32_t Wl, uint32_t R, uint32_t k0,
+                                                       uint32_t k1, int lane, uint32_t grp,
+                                                       const uint32_t* buf, uint32_t* starts, uint32_t* sym) {
   const uint32_t lrem = lane_rem_bits<LAT>(k0, k1);
-  const uint32_t R = h.R;
-  bool ok = h.ok;
-  const uint32_t Wl = ok ? h.W : 0u;
-  if ((uint32_t)lane < Wl) buf[lane] = h.w0;
-  if ((uint32_t)lane + 64u < Wl) buf[lane + 64] = h.w1;
-  for (uint32_t w = 128u + lane; w < Wl; w += 64) buf[w] = A.payload[(uint64_t)h.start + w];
-  if (lane < 2) buf[Wl + lane] = 0u;  // two zero words past the end
+  wave_sync_lds();
   starts[lane] = (lane == 0) ? R : 0xFFFFFFFFu;
   wave_sync_lds();
-
   // unary terminators: popcount prefix over the unary words, then the start
-  // of each lane's codes (just past terminator 8 l - 1)
+  // of each group's codes (just past terminator 8 j - 1)
   const uint32_t uw0 = R >> 5;
   const uint32_t nuw = ok ? Wl - uw0 : 0u;
-  uint32_t pos;
-  if (nuw <= 64u) {
-    // one word per lane: word w holds terminators excl_w .. incl_w - 1, and
-    // lane l >= 1 starts just past terminator 8 l - 1, so word w is the
-    // start word of lanes l in [(excl_w + 8) / 8, incl_w / 8] (at most four,
-    // a word holding at most 32 terminators).  Each word's lane writes its
-    // index and excl_w into those lanes' slots; each lane then reads its own
-    // and selects inside that word.  A lane past the last terminator (8 l >
-    // the total) gets no slot and reports a corrupt sub-stream.
-    const uint32_t v = ((uint32_t)lane < nuw) ? buf[uw0 + lane] : 0u;
+  uint32_t carry = 0;
+  for (uint32_t base = 0; base < nuw; base += 64) {
+    const uint32_t wi = base + lane;
+    const uint32_t v = (wi < nuw) ? buf[uw0 + wi] : 0u;
     const uint32_t cnt = __popc(v);
     const uint32_t incl = wave_scan_incl(cnt);
-    const uint32_t total = __builtin_amdgcn_readlane(incl, 63);
-    const uint32_t excl = incl - cnt;
-    const uint32_t llo = (excl + 8u) >> 3, lhi = incl >> 3;
-    const uint32_t entry = (uint32_t)lane | (excl << 8);
-#pragma unroll
-    for (uint32_t i = 0; i < 4; ++i)
-      if (llo + i <= lhi && llo + i < 64u) starts[llo + i] = entry;
-    wave_sync_lds();
-    const uint32_t target = 8u * (uint32_t)lane;  // terminators before this lane's codes
-    if (lane == 0) {
-      pos = R;
-    } else {
-      ok = ok && target <= total;
-      const uint32_t e = ok ? starts[lane] : 0u;
-      const uint32_t w = e & 0xFFu;
-      const uint32_t word = ok ? buf[uw0 + w] : 0u;
-      pos = ok ? (uw0 + w) * 32u + select32_lut(word, target - 1u - (e >> 8), seltbl) + 1u : 0u;
+    const uint32_t P = carry + incl - cnt;
+    for (uint32_t t = (P & ~7u) + 7u; t < P + cnt; t += 8u) {
+      const uint32_t j = (t + 1u) >> 3;
+      if (j < 64u) starts[j] = (uw0 + wi) * 32u + select32(v, t - P) + 1u;
     }
-  } else {
-    uint32_t carry = 0;
-    for (uint32_t base = 0; base < nuw; base += 64) {
-      const uint32_t wi = base + lane;
-      const uint32_t v = (wi < nuw) ? buf[uw0 + wi] : 0u;
-      const uint32_t cnt = __popc(v);
-      const uint32_t incl = wave_scan_incl(cnt);
-      const uint32_t P = carry + incl - cnt;
-      for (uint32_t t = (P & ~7u) + 7u; t < P + cnt; t += 8u) {
-        const uint32_t j = (t + 1u) >> 3;
-        if (j < 64u) starts[j] = (uw0 + wi) * 32u + select32(v, t - P) + 1u;
-      }
-      carry += __builtin_amdgcn_readlane(incl, 63);
-    }
-    wave_sync_lds();
-    pos = starts[lane];
+    carry += __builtin_amdgcn_readlane(incl, 63);
   }
+  wave_sync_lds();
+  uint32_t pos = starts[grp];
 
   // lane's 8 quotients
   const uint32_t nbits = 32u * Wl;
@@ -1216,7 +1171,7 @@ __device__ __forceinline__ bool decode_symbols(const hq_decode_args& A, const De
     }
   }
   // lane's 8 remainders (fields at fixed positions)
-  const uint32_t rpos = __umul24((uint32_t)lane, lrem);  // lrem < 2^24
+  const uint32_t rpos = __umul24(grp, lrem);  // lrem < 2^24
   if (lrem <= 32) {
     const uint32_t acc = (ok && lrem) ? bits32_at(buf, rpos) : 0u;
 #pragma unroll
@@ -1247,6 +1202,103 @@ __device__ __forceinline__ bool decode_symbols(const hq_decode_args& A, const De
     for (int j = 0; j < 8; ++j) sym[j] = 0u;
   }
   return ok;
+}
+
+// LDS byte address of a pointer into shared memory.
+__device__ __forceinline__ uint32_t lds_addr(const uint32_t* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint32_t*)p;
+}
+
+// a[OFF / 4] = v in the lanes where n > N, without a branch around the store.
+template <int N>
+__device__ __forceinline__ void store_slot(uint32_t a, uint32_t v, int32_t n) {
+  uint64_t saved;
+  asm volatile(
+      "v_cmp_lt_i32 vcc, %4, %3\n\t"
+      "s_and_saveexec_b64 %0, vcc\n\t"
+      "ds_write_b32 %1, %2 offset:%5\n\t"
+      "s_mov_b64 exec, %0"
+      : "=&s"(saved)
+      : "v"(a), "v"(v), "v"(n), "n"(N), "n"(4 * N)
+      : "vcc", "memory");
+}
+
+// The 8 symbols of group `grp` (0 .. 63, a permutation of the lanes) of a
+// sub-stream, into sym; returns the lanes whose parse failed (wave-uniform;
+// any: the sub-stream is corrupt and every symbol is zero).  Almost every
+// sub-stream takes a path with no per-lane branch: it fits the 128 words of
+// its head, its unary codes at most 64, at least 512 terminators are there
+// (so every group's codes exist and end), every group's 8 codes lie in 32
+// bits and its remainders too.  `small` (wave-uniform) then says that every
+// symbol is below 25 2^k with k <= 4.  The others, corrupt ones among them, go
+// through decode_symbols_general.
+template <int LAT>
+__device__ __forceinline__ unsigned long long decode_symbols(const hq_decode_args& A, const DecHead& h, int lane,
+                                                             uint32_t grp, uint32_t* buf, uint32_t* starts,
+                                                             const uint32_t* seltbl, uint32_t* sym, bool& small) {
+  const uint32_t kb = h.kb;
+  const uint32_t k0 = (LAT == kA2) ? (kb & 15u) : kb;
+  const uint32_t k1 = (LAT == kA2) ? (kb >> 4) : (LAT == kD4 ? (k0 > 0 ? k0 - 1 : 0) : k0);
+  const uint32_t lrem = lane_rem_bits<LAT>(k0, k1);
+  const uint32_t R = h.R;
+  const uint32_t Wl = h.ok ? h.W : 0u;
+  const uint32_t uw0 = R >> 5;
+  small = false;
+  // lds_words >= 62: the wave's region holds 128 words (66 follow its buffer)
+  if (h.ok && Wl <= 126u && A.lds_words >= 62u && lrem <= 32u && Wl - uw0 <= 64u) {
+    buf[lane] = h.w0;  // zeros past the end
+    buf[lane + 64] = h.w1;
+    wave_sync_lds();
+    // one unary word per lane (uw0 <= 64): word w holds terminators excl ..
+    // incl - 1, and group j >= 1 starts just past terminator 8 j - 1, so word w
+    // is the start word of groups j in [(excl + 8) / 8, incl / 8] (at most
+    // four).  Each word's lane writes its index and the group's rank among its
+    // terminators into those groups' slots; each lane then reads its group's
+    // and selects inside that word.
+    const uint32_t cnt = __popc(buf[uw0 + lane]);
+    const uint32_t incl = wave_scan_incl(cnt);
+    if (__builtin_amdgcn_readlane(incl, 63) >= 512u) {
+      const uint32_t excl = incl - cnt;
+      const uint32_t e8 = excl + 8u, llo = e8 >> 3;
+      const int32_t m = (int32_t)(min(incl >> 3, 63u) - llo);  // last slot less the first; 64 and beyond are no groups
+      const uint32_t entry = ((uint32_t)lane << 5) + ((e8 & ~7u) - 1u - excl);
+      // the slots lie behind the words that are still read
+      const uint32_t slot = lds_addr(starts) + 4u * llo;
+      store_slot<0>(slot, entry, m + 1);
+      store_slot<1>(slot, entry + 8u, m + 1);
+      store_slot<2>(slot, entry + 16u, m + 1);
+      store_slot<3>(slot, entry + 24u, m + 1);
+      wave_sync_lds();
+      // group 0 begins at bit R and has no slot: its lane reads word 0 and drops the result
+      const uint32_t slot_g = starts[grp];
+      const uint32_t e = grp != 0u ? slot_g : 0u;
+      const uint32_t uw = uw0 + (e >> 5);
+      uint32_t pos = uw * 32u + select32_half(buf[uw], e & 31u, seltbl) + 1u;
+      pos = grp != 0u ? pos : R;
+      const uint32_t win = bits32_at(buf, pos);
+      if (__ballot(__popc(win) < 8) == 0ull) {
+        uint32_t rpos;
+        asm("v_mul_u32_u24 %0, %1, %2" : "=v"(rpos) : "v"(grp), "s"(lrem));
+        const uint32_t acc = bits32_at(buf, rpos);
+        uint32_t sh = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const uint32_t kk = sym_class<LAT>(j) ? k1 : k0;
+          const uint32_t q = (uint32_t)__builtin_ctz(win >> sh);
+          sh += q + 1u;
+          sym[j] = (q << kk) | __builtin_amdgcn_ubfe(acc, rem_offset<LAT>(j, k0, k1), kk);
+        }
+        small = k0 <= 4u && k1 <= 4u;
+        return 0ull;
+      }
+    }
+  } else {
+    if ((uint32_t)lane < Wl) buf[lane] = h.w0;
+    if ((uint32_t)lane + 64u < Wl) buf[lane + 64] = h.w1;
+    for (uint32_t w = 128u + lane; w < Wl; w += 64) buf[w] = A.payload[(uint64_t)h.start + w];
+    if (lane < 2) buf[Wl + lane] = 0u;  // two zero words past the end
+  }
+  return __ballot(!decode_symbols_general<LAT>(h.ok, Wl, R, k0, k1, lane, grp, buf, starts, sym));
 }
 
 // Dynamic LDS above 64 KB needs a per-kernel opt-in, a costly runtime call:

@@ -79,9 +79,10 @@ __global__ __launch_bounds__(256) void hq_decode_gemv_kernel(hq_decode_args A, c
     DecHead next;
     if (j + HQ_WAVES_PER_WG < spr) next = head_of(j + HQ_WAVES_PER_WG);
     uint32_t sym[8];
-    const bool ok = decode_symbols<LAT>(A, head, lane, buf, starts, s_sel, sym);
-    if (!ok && A.stats) {
-      const unsigned long long bad = __ballot(!ok);
+    bool small;
+    const unsigned long long bad =
+        decode_symbols<LAT>(A, head, lane, (uint32_t)lane, buf, starts, s_sel, sym, small);
+    if (bad && A.stats) {
       if ((unsigned)lane == (unsigned)__builtin_ctzll(bad)) {
         atomicAdd(&A.stats->corrupt_substreams, 1u);
         atomicCAS(&A.stats->status, 0u, (uint32_t)HQ_ERR_CORRUPT);
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(256) void hq_decode_gemv_rows_kernel(hq_decode_args
   float acc = 0.0f;
   DecHead head = head_of(0);
   float rs = fp16_norm ? (float)((const _Float16*)A.norms)[t0] : ((const float*)A.norms)[t0];
-  bool bad = false;
+  unsigned long long bad = 0;
   for (uint32_t j = 0; j < spr; ++j) {
     DecHead next;
     float rs_next = 0.0f;
@@ -152,7 +153,8 @@ __global__ __launch_bounds__(256) void hq_decode_gemv_rows_kernel(hq_decode_args
       rs_next = fp16_norm ? (float)((const _Float16*)A.norms)[t] : ((const float*)A.norms)[t];
     }
     uint32_t sym[8];
-    bad |= !decode_symbols<LAT>(A, head, lane, buf, starts, s_sel, sym);
+    bool small;
+    bad |= decode_symbols<LAT>(A, head, lane, (uint32_t)lane, buf, starts, s_sel, sym, small);
     int32_t c[8];
     unstrip8<LAT>(sym, c);
     const int64_t col = (int64_t)j * HQ_SUB + 8 * lane;
@@ -167,8 +169,7 @@ __global__ __launch_bounds__(256) void hq_decode_gemv_rows_kernel(hq_decode_args
     rs = rs_next;
   }
   if (bad && A.stats) {
-    const unsigned long long anyb = __ballot(bad);
-    if ((unsigned)lane == (unsigned)__builtin_ctzll(anyb)) {
+    if ((unsigned)lane == (unsigned)__builtin_ctzll(bad)) {
       atomicAdd(&A.stats->corrupt_substreams, 1u);
       atomicCAS(&A.stats->status, 0u, (uint32_t)HQ_ERR_CORRUPT);
     }
@@ -327,11 +328,12 @@ __global__ __launch_bounds__(256) void hq_attn_prep_kernel(hq_attn_args A) {
 // The lane's 8 coordinates of one coded tile, code - U (U the stream's
 // dither at that row).
 template <int LAT>
-__device__ __forceinline__ bool attn_tile(const hq_decode_args& S, const DecHead& head, int lane,
-                                          uint32_t* buf, uint32_t* starts, const uint32_t* sel,
-                                          uint32_t row, uint32_t j, float* y) {
+__device__ __forceinline__ unsigned long long attn_tile(const hq_decode_args& S, const DecHead& head, int lane,
+                                                        uint32_t* buf, uint32_t* starts, const uint32_t* sel,
+                                                        uint32_t row, uint32_t j, float* y) {
   uint32_t sym[8];
-  const bool ok = decode_symbols<LAT>(S, head, lane, buf, starts, sel, sym);
+  bool small;
+  const unsigned long long bad = decode_symbols<LAT>(S, head, lane, (uint32_t)lane, buf, starts, sel, sym, small);
   int32_t c[8];
   unstrip8<LAT>(sym, c);
 #pragma unroll
@@ -342,11 +344,11 @@ __device__ __forceinline__ bool attn_tile(const hq_decode_args& S, const DecHead
 #pragma unroll
     for (int i = 0; i < 8; ++i) y[i] = y[i] - u[i];
   }
-  if (__ballot(!ok) != 0ull) {  // a corrupt sub-stream contributes zeros
+  if (bad) {  // a corrupt sub-stream contributes zeros
 #pragma unroll
     for (int i = 0; i < 8; ++i) y[i] = 0.0f;
   }
-  return ok;
+  return bad;
 }
 
 // Stored tile norm r of the lane's tile in `row` (fp32 or fp16).
@@ -434,7 +436,7 @@ void hq_attn_kernel(hq_attn_args A) {
   if (VAL && t0 < t1) m = *wmax;  // written by the key pass for these tokens
   const uint32_t bt = (uint32_t)A.block_tokens;
   const int32_t* trow = A.table + (int64_t)b * A.max_blocks;
-  bool bad = false;
+  unsigned long long bad = 0;
   for (int64_t tb = t0; tb < t1; tb += 64) {
     // lane i fetches token tb + i's row and table entry (rows past the
     // streams or a negative block id: row ~0u, the token is skipped)
@@ -474,7 +476,7 @@ void hq_attn_kernel(hq_attn_args A) {
       if (i + 1 < n) fetch(i + 1, nrow, nhd, nnr, nsc);
       if (row != ~0u) {
         float y[8];
-        bad |= !attn_tile<LAT>(S, hd, lane, buf, starts, s_sel, row, j, y);
+        bad |= attn_tile<LAT>(S, hd, lane, buf, starts, s_sel, row, j, y);
         const float gs = nr / S.alpha_n;
         if constexpr (!VAL) {
           float d[G];
@@ -513,8 +515,7 @@ void hq_attn_kernel(hq_attn_args A) {
     }
   }
   if (bad && A.K.stats) {
-    const unsigned long long anyb = __ballot(bad);
-    if ((unsigned)lane == (unsigned)__builtin_ctzll(anyb)) {
+    if ((unsigned)lane == (unsigned)__builtin_ctzll(bad)) {
       atomicAdd(&A.K.stats->corrupt_substreams, 1u);
       atomicCAS(&A.K.stats->status, 0u, (uint32_t)HQ_ERR_CORRUPT);
     }
@@ -770,9 +771,7 @@ __global__ __launch_bounds__(256) void hq_act_prep_kernel(hq_actprep_args A) {
       am = __builtin_fmaxf(am, __shfl_xor(am, 2, 64));
       am = __builtin_fmaxf(am, __shfl_xor(am, 4, 64));
       const int32_t X = mx_exponent(am);
-      uint32_t packed = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) packed |= e2m1_code(__builtin_ldexpf(q[i], -X)) << (4 * i);
+      const uint32_t packed = e2m1_pair<1>(e2m1_pair<0>(0u, q[0], q[1], X), q[2], q[3], X);
       if (in) {
         *(uint16_t*)((uint8_t*)A.xq + row * (A.K / 2) + col / 2) = (uint16_t)packed;
         if ((tid & 7) == 0) A.mxs[row * (A.K / 32) + col / 32] = (uint8_t)(X + 127);
