@@ -88,7 +88,7 @@ __device__ __forceinline__ void store_stream(void* p, uint4 v) {
 // fill the chip with four per wave.
 template <int LAT, int MODE, bool KV, int SPW = HQ_DEC_SUBS_PER_WAVE>
 __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_t wgi) {
-  extern __shared__ uint32_t smem[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   __shared__ uint32_t s_sel[256];
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = readfirst((uint32_t)(tid >> 6));
@@ -385,7 +385,7 @@ __device__ __forceinline__ bool decode_block_mb(const uint32_t* buf, uint32_t Wl
 // A corrupt sub-stream's codes count as zeros in its tile.
 template <int LAT, int MODE>
 __device__ __forceinline__ void decode_wg_tiled(const hq_decode_args& A, const uint32_t wgi) {
-  extern __shared__ uint32_t smem[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   __shared__ uint32_t s_sel[256];
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = readfirst((uint32_t)(tid >> 6));
@@ -549,7 +549,7 @@ constexpr int kQjlTiles = 64;           // tiles per workgroup pass (16 sub-stre
 
 template <int LAT, int MODE>
 __global__ __launch_bounds__(256) void hq_decode_qjl_kernel(hq_decode_args A) {
-  extern __shared__ uint32_t smem[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   __shared__ uint32_t s_sel[256];
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = readfirst((uint32_t)(tid >> 6));

@@ -352,16 +352,15 @@ __device__ __forceinline__ float code_coord(int32_t c, int j) {
 }
 
 // E8's U = b - Q(b) for a box point b in [-2, 2)^8 whose coordinates are
-// multiples of 2^-22: the point quant_e8 picks, without its roundings and
-// branches.  Every coset error is exact here: the even coset's is
-// b - 2 rint(b / 2) (rint by the 1.5 * 2^23 shift, whose low bit is k's
-// parity), the odd coset's b - sign(b) (floor(b / 2) is 0 or -1), and
-// neither is ever -0.  A coset whose parity is odd moves its first
-// coordinate of largest error to the next point on the other side, which
-// turns that error e into e - 2 sign(e); the squared errors are summed in
-// the same fp32 tree as quant_e8's, and U is the nearer coset's error vector
-// (the even one on a tie).
-__device__ __forceinline__ void dither_e8(const float* b, float* u) {
+// multiples of 2^-22: the point quant_e8 picks.  The even coset's error is
+// ea = b - 2 rint(b / 2) (rint by the 1.5 * 2^23 shift, whose low bit is the
+// rounded value's parity), the odd coset's b - sign(b); both are exact and
+// never -0.  A coset whose parity is odd moves its first coordinate of largest
+// error to the next point on the other side, which turns that error e into e -
+// 2 sign(e); U is the nearer coset's error vector (the even one on a tie, the
+// squared errors summed in quant_e8's fp32 tree).  This form carries both
+// vectors out; it is the reference of dither_e8.
+__device__ __forceinline__ void dither_e8_cosets(const float* b, float* u) {
   constexpr float kShift = 12582912.0f;  // 1.5 * 2^23
   float ea[8], eb[8];
   uint32_t pa = 0, pb = 0;
@@ -398,6 +397,55 @@ __device__ __forceinline__ void dither_e8(const float* b, float* u) {
   const bool even = tree8(sa) <= tree8(sq);
 #pragma unroll
   for (int i = 0; i < 8; ++i) u[i] = even ? ea[i] : eb[i];
+}
+
+// The same point from the even coset's errors alone.  The odd one's are ea -
+// sign(ea), so |eb| = 1 - |ea|: its largest is the smallest |ea|, and the two
+// squared distances differ by
+//   D = 8 - 2 sum |ea| + [odd coset's parity] 4 min |ea| - [even's] (4 - 4 max |ea|),
+// whose sign is the decision wherever rounding cannot matter (the trees' and
+// D's errors stay below 2^-15).  Then one pass adds the chosen coset's offset,
+// 0 or -sign(ea), and at the moved coordinate -2 sign(ea) or +sign(ea).  A wave
+// with a lane near a tie, or at the box's all-odd points (min |ea| = 1, where
+// sign(eb) is not -sign(ea)), takes the two-coset form: about 0.3 % of them.
+// Against it, half the passes over the 8 coordinates and no squares: KV decode
+// of 32768 x 1024 rows 53.1 -> 49.1 us, 16 x 8192-token attention 465 -> 434.
+__device__ __forceinline__ void dither_e8(const float* b, float* u) {
+  constexpr float kShift = 12582912.0f;  // 1.5 * 2^23
+  float ea[8];
+  uint32_t tb[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float t = b[i] * 0.5f + kShift;
+    ea[i] = __builtin_fmaf(-2.0f, t - kShift, b[i]);
+    tb[i] = __float_as_uint(t);
+  }
+  const uint32_t pa = xor3(xor3(tb[0], tb[1], tb[2]), tb[3], tb[4]) ^ xor3(tb[5], tb[6], tb[7]);
+  const uint32_t pb = xor3(xor3(__float_as_uint(b[0]), __float_as_uint(b[1]), __float_as_uint(b[2])),
+                           __float_as_uint(b[3]), __float_as_uint(b[4])) ^
+                      xor3(__float_as_uint(b[5]), __float_as_uint(b[6]), __float_as_uint(b[7]));
+  float a[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = __builtin_fabsf(ea[i]);
+  const float mx = fmaxf(fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])), fmaxf(fmaxf(a[4], a[5]), fmaxf(a[6], a[7])));
+  const float mn = fminf(fminf(fminf(a[0], a[1]), fminf(a[2], a[3])), fminf(fminf(a[4], a[5]), fminf(a[6], a[7])));
+  const bool oa = pa & 1u, ob = pb >> 31;
+  const float D = __builtin_fmaf(-2.0f, tree8(a), 8.0f) + ((ob ? 4.0f * mn : 0.0f) - (oa ? 4.0f - 4.0f * mx : 0.0f));
+  if (__ballot(__builtin_fabsf(D) < 0x1p-13f || mn >= 1.0f) != 0ull) {
+    dither_e8_cosets(b, u);
+    return;
+  }
+  const bool even = D > 0.0f;
+  const float target = even ? (oa ? mx : 2.0f) : (ob ? mn : 2.0f);  // 2: no |ea| is, nothing moves
+  const float base = even ? 0.0f : -1.0f, moved = even ? -2.0f : 1.0f;
+  bool done = false;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const bool hit = !done && a[i] == target;
+    done = done || hit;
+    const float t = hit ? moved : base;
+    u[i] = ea[i] + __uint_as_float(__float_as_uint(t) ^ (__float_as_uint(ea[i]) & 0x80000000u));
+  }
 }
 
 // Dither U = b - Q(b) for the lane's 8 coordinates (columns col0 .. col0+7 of
@@ -647,6 +695,49 @@ __device__ __forceinline__ void qjl_tile(const float* __restrict__ Mt, float* st
   wave_lds_sync();  // every lane has read the stage before it is written again
 #pragma unroll
   for (int i = 0; i < 8; ++i) v[i] = acc[i];
+}
+
+// The same rotation by a whole wave, its four tiles together: lane l forms
+// outputs 2 l and 2 l + 1 of every tile, so a row of M^T (512 bytes over the
+// wave) is read once for the four tiles and the tiles' k-th values come as one
+// broadcast; the sums go back through `stage`.  Each output is the same
+// left-to-right sum.  qjl_tile's lanes each load 32 bytes of M^T per k, the
+// wave 2 KB, and the 64 bytes a clock at which a CU's cache returns data
+// bound it: 2048 x 1024 rows appended in 41.4 us, 27.9 here.  `stage` is 16-byte
+// aligned (a kernel's dynamic LDS is declared so): a misaligned b128 read takes
+// about 64 cycles instead of 8 (70.6 us).
+__device__ __forceinline__ void qjl_wave(const float* __restrict__ Mt, float* stage, int lane, float* v) {
+  // z of tile t at stage[4 k + t]
+  const int t0 = lane >> 4, c0 = (lane & 15) * 8;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) stage[4 * (c0 + i) + t0] = v[i];
+  wave_lds_sync();
+  float acc[4][2];
+  {
+    const float2 m = *(const float2*)(Mt + 2 * lane);
+    const float4 z = *(const float4*)stage;
+    acc[0][0] = m.x * z.x; acc[0][1] = m.y * z.x;
+    acc[1][0] = m.x * z.y; acc[1][1] = m.y * z.y;
+    acc[2][0] = m.x * z.z; acc[2][1] = m.y * z.z;
+    acc[3][0] = m.x * z.w; acc[3][1] = m.y * z.w;
+  }
+#pragma unroll 8
+  for (int k = 1; k < HQ_TILE; ++k) {
+    const float2 m = *(const float2*)(Mt + k * HQ_TILE + 2 * lane);
+    const float4 z = *(const float4*)(stage + 4 * k);
+    acc[0][0] = acc[0][0] + m.x * z.x; acc[0][1] = acc[0][1] + m.y * z.x;
+    acc[1][0] = acc[1][0] + m.x * z.y; acc[1][1] = acc[1][1] + m.y * z.y;
+    acc[2][0] = acc[2][0] + m.x * z.z; acc[2][1] = acc[2][1] + m.y * z.z;
+    acc[3][0] = acc[3][0] + m.x * z.w; acc[3][1] = acc[3][1] + m.y * z.w;
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int t = 0; t < 4; ++t) *(float2*)(stage + t * HQ_TILE + 2 * lane) = make_float2(acc[t][0], acc[t][1]);
+  wave_lds_sync();
+  const float4 a = *(const float4*)(stage + t0 * HQ_TILE + c0), b = *(const float4*)(stage + t0 * HQ_TILE + c0 + 4);
+  wave_lds_sync();  // every lane has read the stage before it is written again
+  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+  v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
 // ------------------------------------------------------------ look-back scan

@@ -265,7 +265,7 @@ __device__ __forceinline__ void encode_substream(const hq_encode_args& A, const 
   }
   // z <- S z, S^T read from global memory (a workgroup copy in LDS measured
   // 3x slower on the one-sub-stream-per-wave appends)
-  if (KV && A.rotation == HQ_ROT_QJL) qjl_tile(A.qjlt, stage, lane, x);
+  if (KV && A.rotation == HQ_ROT_QJL) qjl_wave(A.qjlt, stage, lane, x);
   if (use_dither) {
     float u[8];
     dither8<LAT>(A.dither_seed, grow, col, u);
@@ -567,7 +567,7 @@ __device__ __forceinline__ void encode_wg(const hq_encode_args& A, const hq_rice
   static_assert(MB == 1 || (TILED && (MB == 2 || MB == 4)), "multi-block sub-streams: long-tile front end");
   constexpr int NSUB = HQ_ENC_SUBS_PER_WG;  // sub-streams per workgroup
   constexpr int WAVES = NSUB / SPW;         // wave64s per workgroup
-  extern __shared__ uint32_t smem[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   __shared__ uint32_t s_epoch;
   __shared__ uint32_t s_words[NSUB];
   __shared__ uint32_t s_pad[WAVES];

@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void hq_gemv_prep_kernel(const void* x, int x_
 template <int LAT>
 __global__ __launch_bounds__(256) void hq_decode_gemv_kernel(hq_decode_args A, const float* xt,
                                                              void* y, int y_bf16) {
-  extern __shared__ uint32_t smem[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   __shared__ uint32_t s_sel[256];
   __shared__ float s_part[HQ_WAVES_PER_WG];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void hq_decode_gemv_kernel(hq_decode_args A, c
 template <int LAT>
 __global__ __launch_bounds__(256) void hq_decode_gemv_rows_kernel(hq_decode_args A, const float* xt,
                                                                   void* y, int y_bf16, int64_t rows) {
-  extern __shared__ uint32_t smem[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   __shared__ uint32_t s_sel[256];
   const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t wave = readfirst((uint32_t)(tid >> 6));
@@ -386,7 +386,7 @@ __device__ __forceinline__ uint32_t lane_val(uint32_t v, uint32_t i) {
 template <int LAT, int G, bool VAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(VAL && G <= 4 ? 4 : 1)))
 void hq_attn_kernel(hq_attn_args A) {
-  extern __shared__ uint32_t smem[];
+  extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
   __shared__ uint32_t s_sel[256];
   __shared__ float s_m[HQ_WAVES_PER_WG][4 * G];
   __shared__ float s_l[HQ_WAVES_PER_WG][4 * G];
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(256) void hq_attn_combine_kernel(hq_attn_args A) {
 // longer tile h = 128 .. tile / 2 in LDS), amax over the row, then the cast.
 
 __global__ __launch_bounds__(256) void hq_act_prep_kernel(hq_actprep_args A) {
-  extern __shared__ float ybuf[];
+  extern __shared__ __attribute__((aligned(16))) float ybuf[];
   __shared__ float s_max[4];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int64_t row = blockIdx.x;

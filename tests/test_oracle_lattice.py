@@ -230,3 +230,33 @@ def test_gaps_and_gains_match_paper():
         assert abs(gap[l] - v) < 0.011
     gain = {lat: 10 * np.log10(O.nsm(O.Z) / O.nsm(lat)) for lat in LATS}
     assert [round(gain[l], 2) for l in (O.A2, O.D4, O.E8)] == [0.17, 0.37, 0.65]
+
+
+@pytest.mark.parametrize("step", [2.0 ** -22, 2.0 ** -6, 2.0 ** -2, 2.0 ** -1, 1.0])
+def test_e8_box_point_from_even_errors(step):
+    """The E8 dither point's closed form on its box against the general decoder: the odd coset's
+    errors are ea - sign(ea), D's sign decides away from ties, one moved coordinate ends it.  The
+    coarse steps make ties and equal magnitudes; blocks in the tie band (or with every |ea| = 1) are
+    the two-coset form's and are left out, as the kernels do."""
+    rng = np.random.default_rng(int(1 / step))
+    n = int(4 / step)
+    b = (rng.integers(0, n, (200000, 8)) * step - 2.0).astype(np.float32)
+    u = b - O.quantize(O.E8, b).astype(np.float32)
+    t = b * np.float32(0.5) + np.float32(12582912.0)
+    ea = b - np.float32(2.0) * (t - np.float32(12582912.0))
+    assert not np.any(np.signbit(ea) & (ea == 0))
+    a = np.abs(ea)
+    odd_a = np.bitwise_xor.reduce(t.view(np.uint32), axis=1) & 1 == 1
+    odd_b = np.signbit(b).sum(axis=1) % 2 == 1
+    mx, mn = a.max(axis=1), a.min(axis=1)
+    D = 8 - 2 * a.astype(np.float64).sum(axis=1) + np.where(odd_b, 4 * mn, 0) - np.where(odd_a, 4 - 4 * mx, 0)
+    ok = (np.abs(D) >= 2.0 ** -13) & (mn < 1)
+    even = D > 0
+    target = np.where(even, np.where(odd_a, mx, 2), np.where(odd_b, mn, 2))
+    add = np.repeat(np.where(even, 0.0, -1.0)[:, None], 8, axis=1)
+    hit = a == target[:, None]
+    rows = np.nonzero(hit.any(axis=1))[0]
+    add[rows, hit[rows].argmax(axis=1)] = np.where(even[rows], -2.0, 1.0)
+    v = ea + (add * np.where(np.signbit(ea), -1, 1)).astype(np.float32)
+    assert ok.sum() > (1000 if step < 1 else 0)
+    assert np.array_equal(u[ok], v[ok])
