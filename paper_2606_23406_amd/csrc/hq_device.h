@@ -721,7 +721,7 @@ __device__ __forceinline__ void qjl_wave(const float* __restrict__ Mt, float* st
     acc[2][0] = m.x * z.z; acc[2][1] = m.y * z.z;
     acc[3][0] = m.x * z.w; acc[3][1] = m.y * z.w;
   }
-#pragma unroll 8
+#pragma unroll 4  // eight take 22 more registers and cost the other rotations waves
   for (int k = 1; k < HQ_TILE; ++k) {
     const float2 m = *(const float2*)(Mt + k * HQ_TILE + 2 * lane);
     const float4 z = *(const float4*)(stage + 4 * k);

@@ -838,6 +838,7 @@ static hq_status act_prep(hq_plan_t p, const void* a, int64_t M, int64_t lda, in
   args.xq = xq;
   args.sx = sx;
   args.dmask = p->d_dmask;
+  args.dsign16 = p->d_dsign16;
   args.fp8 = fp8;
   args.mxs = mxs;
   args.tile = p->tile;

@@ -172,6 +172,7 @@ struct hq_actprep_args {
   int8_t* xq;             // int8, or E4M3 bytes when fp8
   float* sx;
   const uint32_t* dmask;
+  const uint32_t* dsign16;  // RHT signs as bf16 XOR words, one per column pair
   int32_t fp8;            // 1: E4M3 at 448 / amax instead of int8 at 127 / amax;
                           // 2: MXFP4 (E2M1 pairs per byte, E8M0 scale per 32 in mxs)
   uint8_t* mxs;           // MXFP4: scale bytes (M x K / 32)
