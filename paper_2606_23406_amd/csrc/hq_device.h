@@ -452,8 +452,9 @@ __device__ __forceinline__ void dither_e8(const float* b, float* u) {
 // global row `row`, col0 a multiple of 8): b is a uniform point of a box that
 // is a fundamental domain of a sublattice ([-2, 2)^m for 2E8, D4, Z;
 // [-sqrt3, sqrt3) x [-1, 1) for A2), drawn from 24 bits of Philox word
-// (col mod 4) at counter (col / 4, row_lo, row_hi, 0).
-template <int LAT>
+// (col mod 4) at counter (col / 4, row_lo, row_hi, 0).  COSETS: E8's point from
+// both cosets' errors.
+template <int LAT, bool COSETS = false>
 __device__ __forceinline__ void dither8(uint64_t seed, int64_t row, int64_t col0, float* u) {
   uint32_t r[8];
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
@@ -471,7 +472,10 @@ __device__ __forceinline__ void dither8(uint64_t seed, int64_t row, int64_t col0
     }
   }
   if constexpr (LAT == kE8) {
-    dither_e8(b, u);
+    if constexpr (COSETS)
+      dither_e8_cosets(b, u);
+    else
+      dither_e8(b, u);
   } else {
     int32_t c[8];
     quantize8<LAT>(b, c);
@@ -1185,36 +1189,40 @@ __device__ __forceinline__ uint32_t select32_half(uint32_t w, uint32_t r, const 
 }
 
 // decode_symbols' general path, for group `grp` of a sub-stream of Wl words
-// already in `buf`: any code length, corrupt sub-streams too.  A corrupt
+// already in `buf`: any code length, corrupt sub-streams too.  `known` (wave-
+// uniform): the group's codes start at `pos`, else it is searched.  A corrupt
 // sub-stream (any lane's parse failed) decodes as all-zero symbols in every
 // lane; callers drop its factor too.
 template <int LAT>
 __device__ __forceinline__ bool decode_symbols_general(bool ok, uint32_t Wl, uint32_t R, uint32_t k0,
-                                                       uint32_t k1, int lane, uint32_t grp,
-                                                       const uint32_t* buf, uint32_t* starts, uint32_t* sym) {
+                                                       uint32_t k1, int lane, uint32_t grp, bool known,
+                                                       uint32_t pos, const uint32_t* buf, uint32_t* starts,
+                                                       uint32_t* sym) {
   const uint32_t lrem = lane_rem_bits<LAT>(k0, k1);
-  wave_sync_lds();
-  starts[lane] = (lane == 0) ? R : 0xFFFFFFFFu;
-  wave_sync_lds();
-  // unary terminators: popcount prefix over the unary words, then the start
-  // of each group's codes (just past terminator 8 j - 1)
-  const uint32_t uw0 = R >> 5;
-  const uint32_t nuw = ok ? Wl - uw0 : 0u;
-  uint32_t carry = 0;
-  for (uint32_t base = 0; base < nuw; base += 64) {
-    const uint32_t wi = base + lane;
-    const uint32_t v = (wi < nuw) ? buf[uw0 + wi] : 0u;
-    const uint32_t cnt = __popc(v);
-    const uint32_t incl = wave_scan_incl(cnt);
-    const uint32_t P = carry + incl - cnt;
-    for (uint32_t t = (P & ~7u) + 7u; t < P + cnt; t += 8u) {
-      const uint32_t j = (t + 1u) >> 3;
-      if (j < 64u) starts[j] = (uw0 + wi) * 32u + select32(v, t - P) + 1u;
+  if (!known) {
+    wave_sync_lds();
+    starts[lane] = (lane == 0) ? R : 0xFFFFFFFFu;
+    wave_sync_lds();
+    // unary terminators: popcount prefix over the unary words, then the start
+    // of each group's codes (just past terminator 8 j - 1)
+    const uint32_t uw0 = R >> 5;
+    const uint32_t nuw = ok ? Wl - uw0 : 0u;
+    uint32_t carry = 0;
+    for (uint32_t base = 0; base < nuw; base += 64) {
+      const uint32_t wi = base + lane;
+      const uint32_t v = (wi < nuw) ? buf[uw0 + wi] : 0u;
+      const uint32_t cnt = __popc(v);
+      const uint32_t incl = wave_scan_incl(cnt);
+      const uint32_t P = carry + incl - cnt;
+      for (uint32_t t = (P & ~7u) + 7u; t < P + cnt; t += 8u) {
+        const uint32_t j = (t + 1u) >> 3;
+        if (j < 64u) starts[j] = (uw0 + wi) * 32u + select32(v, t - P) + 1u;
+      }
+      carry += __builtin_amdgcn_readlane(incl, 63);
     }
-    carry += __builtin_amdgcn_readlane(incl, 63);
+    wave_sync_lds();
+    pos = starts[grp];
   }
-  wave_sync_lds();
-  uint32_t pos = starts[grp];
 
   // lane's 8 quotients
   const uint32_t nbits = 32u * Wl;
@@ -1335,6 +1343,8 @@ __device__ __forceinline__ unsigned long long decode_symbols(const hq_decode_arg
   const uint32_t Wl = h.ok ? h.W : 0u;
   const uint32_t uw0 = R >> 5;
   small = false;
+  bool known = false;
+  uint32_t pos = 0;
   // lds_words >= 62: the wave's region holds 128 words (66 follow its buffer)
   if (h.ok && Wl <= 126u && A.lds_words >= 62u && lrem <= 32u && Wl - uw0 <= 64u) {
     buf[lane] = h.w0;  // zeros past the end
@@ -1364,7 +1374,7 @@ __device__ __forceinline__ unsigned long long decode_symbols(const hq_decode_arg
       const uint32_t slot_g = starts[grp];
       const uint32_t e = grp != 0u ? slot_g : 0u;
       const uint32_t uw = uw0 + (e >> 5);
-      uint32_t pos = uw * 32u + select32_half(buf[uw], e & 31u, seltbl) + 1u;
+      pos = uw * 32u + select32_half(buf[uw], e & 31u, seltbl) + 1u;
       pos = grp != 0u ? pos : R;
       const uint32_t win = bits32_at(buf, pos);
       if (__ballot(__popc(win) < 8) == 0ull) {
@@ -1382,6 +1392,7 @@ __device__ __forceinline__ unsigned long long decode_symbols(const hq_decode_arg
         small = k0 <= 4u && k1 <= 4u;
         return 0ull;
       }
+      known = true;
     }
   } else {
     if ((uint32_t)lane < Wl) buf[lane] = h.w0;
@@ -1389,7 +1400,7 @@ __device__ __forceinline__ unsigned long long decode_symbols(const hq_decode_arg
     for (uint32_t w = 128u + lane; w < Wl; w += 64) buf[w] = A.payload[(uint64_t)h.start + w];
     if (lane < 2) buf[Wl + lane] = 0u;  // two zero words past the end
   }
-  return __ballot(!decode_symbols_general<LAT>(h.ok, Wl, R, k0, k1, lane, grp, buf, starts, sym));
+  return __ballot(!decode_symbols_general<LAT>(h.ok, Wl, R, k0, k1, lane, grp, known, pos, buf, starts, sym));
 }
 
 // Dynamic LDS above 64 KB needs a per-kernel opt-in, a costly runtime call:
