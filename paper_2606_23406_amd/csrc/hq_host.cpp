@@ -647,13 +647,27 @@ static int64_t attn_scores_floats(int64_t heads, int64_t max_tokens) {
   return (heads * max_tokens + 3) & ~(int64_t)3;
 }
 
+// Splits of all heads together: at least what any call of up to these sizes
+// uses.  heads * attn_splits itself falls where the chunk steps up (4 to 5
+// tokens a wave: by a fifth), and a workspace kept for the largest call has to
+// serve every smaller one.  A chunk is at least 4, so a head has at most
+// max_tokens / 16 splits (rounded up).  It is also 1024, or at least work /
+// 16384, which leaves all heads together heads_q / spr * 4096 splits beside
+// the one each that rounding adds.
+static int64_t attn_head_splits(const hq_plan_s* k, int64_t batch, int64_t heads_q, int64_t max_tokens) {
+  const int64_t heads = batch * heads_q;
+  const int64_t fixed = heads + (heads_q * 4096 + k->spr - 1) / k->spr;
+  return std::min(heads * attn_splits(max_tokens, 4),
+                  std::max(fixed, heads * attn_splits(max_tokens, 1024)));
+}
+
 size_t hq_attention_workspace_bytes(hq_plan_t k, int64_t batch, int32_t heads_q,
                                     int64_t max_tokens) {
   if (!k || batch < 0 || heads_q <= 0 || max_tokens <= 0) return 0;
-  const int64_t nx = attn_splits(max_tokens, attn_chunk(k, batch, max_tokens));
+  const int64_t parts = attn_head_splits(k, batch, heads_q, max_tokens);
   const int64_t heads = batch * heads_q;
-  return (size_t)(heads * HQ_TILE + heads * nx * HQ_TILE + attn_scores_floats(heads, max_tokens) +
-                  heads * nx * (HQ_WAVES_PER_WG + 2)) *
+  return (size_t)(heads * HQ_TILE + parts * HQ_TILE + attn_scores_floats(heads, max_tokens) +
+                  parts * (HQ_WAVES_PER_WG + 2)) *
          sizeof(float);
 }
 
