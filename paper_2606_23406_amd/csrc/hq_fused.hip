@@ -714,8 +714,9 @@ __global__ __launch_bounds__(256) void hq_attn_combine_kernel(hq_attn_args A) {
 // through LDS (MXFP4's blocks are four lanes: nothing does).  CAST 0 int8, 1
 // E4M3, 2 MXFP4.  int8's values carry the twisted transform's lane sign, which
 // the scale takes back (rounding is symmetric); the other two codes keep the
-// sign of a zero, so they take the plain transform.  4096 x 4096 to int8: 20 -> 13 us
-// (3.9 TB/s), 1000 x 14336 to E4M3 19 -> 12 us against the LDS form below.
+// sign of a zero, so they take the plain transform.  4096 x 4096 to int8: 17.0 -> 13.9
+// us (3.6 TB/s), 1000 x 14336 to E4M3 21.3 -> 16.0, 2048 x 4096 to MXFP4 12.3 ->
+// 10.8 against the LDS form below.
 template <int NIT, int CAST>
 __global__ __launch_bounds__(256) void hq_act_prep_regs_kernel(hq_actprep_args A) {
   __shared__ float s_max[4];
