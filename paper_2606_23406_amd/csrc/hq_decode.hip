@@ -857,27 +857,33 @@ int hq_launch_decode_int8(const hq_plan_s* p, const hq_decode_args& a, void* str
   }
 }
 
-int hq_launch_decode_mxfp4(const hq_plan_s* p, const hq_decode_args& a, void* stream) {
-  hipStream_t st = (hipStream_t)stream;
+// The fp8 (mode 3) and MXFP4 (mode 4) casts; a plan of fp16 norms takes the KV
+// form, which reads them as such.
+template <int MODE>
+static int launch_decode_cast(const hq_plan_s* p, const hq_decode_args& a, hipStream_t st) {
   const size_t lds = (size_t)(a.lds_words + 66) * HQ_WAVES_PER_WG * sizeof(uint32_t);
   const uint32_t nwg = decode_wgs(a.nsub);
+  const bool kv = kv_variant(p);
   switch (p->lattice) {
-    case HQ_E8: launch_decode_kernel<kE8, 4, false>(a, nwg, lds, st); break;
-    case HQ_D4: launch_decode_kernel<kD4, 4, false>(a, nwg, lds, st); break;
-    default: launch_decode_kernel<kZ, 4, false>(a, nwg, lds, st);
+    case HQ_E8:
+      if (kv) launch_decode_kernel<kE8, MODE, true>(a, nwg, lds, st);
+      else launch_decode_kernel<kE8, MODE, false>(a, nwg, lds, st);
+      break;
+    case HQ_D4:
+      if (kv) launch_decode_kernel<kD4, MODE, true>(a, nwg, lds, st);
+      else launch_decode_kernel<kD4, MODE, false>(a, nwg, lds, st);
+      break;
+    default:
+      if (kv) launch_decode_kernel<kZ, MODE, true>(a, nwg, lds, st);
+      else launch_decode_kernel<kZ, MODE, false>(a, nwg, lds, st);
   }
   return (int)hipGetLastError();
+}
+
+int hq_launch_decode_mxfp4(const hq_plan_s* p, const hq_decode_args& a, void* stream) {
+  return launch_decode_cast<4>(p, a, (hipStream_t)stream);
 }
 
 int hq_launch_decode_fp8(const hq_plan_s* p, const hq_decode_args& a, void* stream) {
-  hipStream_t st = (hipStream_t)stream;
-  const size_t lds = (size_t)(a.lds_words + 66) * HQ_WAVES_PER_WG * sizeof(uint32_t);
-  const uint32_t nwg = decode_wgs(a.nsub);
-  switch (p->lattice) {
-    case HQ_E8: launch_decode_kernel<kE8, 3, false>(a, nwg, lds, st); break;
-    case HQ_D4: launch_decode_kernel<kD4, 3, false>(a, nwg, lds, st); break;
-    default: launch_decode_kernel<kZ, 3, false>(a, nwg, lds, st);
-  }
-  return (int)hipGetLastError();
+  return launch_decode_cast<3>(p, a, (hipStream_t)stream);
 }
-
