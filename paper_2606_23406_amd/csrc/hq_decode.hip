@@ -207,19 +207,11 @@ __device__ __forceinline__ void decode_wg(const hq_decode_args& A, const uint32_
       // lanes, inside one tile) share X = floor(log2 amax) - 2, and each value
       // becomes E2M1(v / 2^X), two per byte (the even k in the low nibble),
       // the scale byte X + 127
-      float v[8], am = 0.0f;
+      float v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        v[j] = (float)c[j] * g;
-        am = __builtin_fmaxf(am, __builtin_fabsf(v[j]));
-      }
-      am = __builtin_fmaxf(am, dpp_xor<1>(am));
-      am = __builtin_fmaxf(am, dpp_xor<2>(am));
-      const int32_t X = mx_exponent(am);
-      uint32_t packed = e2m1_pair<0>(0u, v[0], v[1], X);
-      packed = e2m1_pair<1>(packed, v[2], v[3], X);
-      packed = e2m1_pair<2>(packed, v[4], v[5], X);
-      packed = e2m1_pair<3>(packed, v[6], v[7], X);
+      for (int j = 0; j < 8; ++j) v[j] = (float)c[j] * g;
+      int32_t X;
+      const uint32_t packed = mxfp4_x8(v, X);
       uint8_t* out = (uint8_t*)A.y + (int64_t)lrow * A.ld + (col >> 1);
       *(uint32_t*)out = packed;
       if ((lane & 3) == 0) A.mxs[(int64_t)lrow * (A.spr * (HQ_SUB / 32)) + (col >> 5)] = (uint8_t)(X + 127);

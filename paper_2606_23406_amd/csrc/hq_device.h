@@ -644,10 +644,34 @@ __device__ __forceinline__ uint32_t e4m3x4(float a, float b, float c, float d) {
 // the low nibble: the nearest value, ties to the even code, saturating at 6,
 // the sign kept also when a value rounds to zero.  The instruction's scale
 // operand is the float 2^X, of which it takes the exponent field (0 for the
-// block exponent -127).
+// block exponent -127).  It gives NaN the code of 6: see e2m1_drop_nan.
 template <int SEL>
 __device__ __forceinline__ uint32_t e2m1_pair(uint32_t r, float a, float b, int32_t X) {
   return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, a, b, __uint_as_float((uint32_t)(X + 127) << 23), SEL);
+}
+
+// Eight values in one word, the first in the lowest nibble.
+__device__ __forceinline__ uint32_t e2m1_x8(const float* v, int32_t X) {
+  uint32_t r = e2m1_pair<0>(0u, v[0], v[1], X);
+  r = e2m1_pair<1>(r, v[2], v[3], X);
+  r = e2m1_pair<2>(r, v[4], v[5], X);
+  return e2m1_pair<3>(r, v[6], v[7], X);
+}
+
+// NaN is cast to a zero of its sign.
+template <int N>
+__device__ __forceinline__ void e2m1_drop_nan(float* v) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = v[i] != v[i] ? __builtin_copysignf(0.0f, v[i]) : v[i];
+}
+
+// The largest magnitude of a lane's N values, NaN where one of them is.
+template <int N>
+__device__ __forceinline__ float amax_or_nan(const float* v) {
+  float am = 0.0f;
+#pragma unroll
+  for (int i = 0; i < N; ++i) am = __builtin_elementwise_maximum(am, __builtin_fabsf(v[i]));
+  return am;
 }
 
 // The MX block exponent X = floor(log2 amax) - 2 of a block whose largest
@@ -867,6 +891,26 @@ template <int M>
 __device__ __forceinline__ float dpp_xor(float v) {
   constexpr int ctrl = M == 1 ? kDppQuadXor1 : (M == 2 ? kDppQuadXor2 : kDppRowRor8);
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ctrl, 0xF, 0xF, true));
+}
+
+// MXFP4 of a wave's values, eight a lane, 32-blocks of four neighbouring lanes:
+// the lane's word of codes and its block's X.  The test for NaN stands behind
+// the cast, which it repeats without it: before it, or once behind all blocks
+// of a row, it cost the prep of some row lengths 7 to 11 %.
+__device__ __forceinline__ uint32_t mxfp4_x8(float* v, int32_t& X) {
+  const float am0 = amax_or_nan<8>(v);
+  auto cast = [&](float am) {
+    am = __builtin_fmaxf(am, dpp_xor<1>(am));
+    am = __builtin_fmaxf(am, dpp_xor<2>(am));
+    X = mx_exponent(am);
+    return e2m1_x8(v, X);
+  };
+  uint32_t r = cast(am0);
+  if (__builtin_expect(__ballot(am0 != am0) != 0ull, 0)) {
+    e2m1_drop_nan<8>(v);
+    r = cast(amax_or_nan<8>(v));
+  }
+  return r;
 }
 
 // Stage signs of a lane (h = 8, 16, 32, 64 <-> lane bits 0..3) and sigma's

@@ -749,17 +749,8 @@ __global__ __launch_bounds__(256) void hq_act_prep_regs_kernel(hq_actprep_args A
     else
       fwht128(v[i], sg);
     if constexpr (CAST == 2) {
-      // 32-blocks (four lanes) share X = floor(log2 amax) - 2 and hold E2M1(y / 2^X)
-      float am = 0.0f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) am = __builtin_fmaxf(am, __builtin_fabsf(v[i][e]));
-      am = __builtin_fmaxf(am, dpp_xor<1>(am));
-      am = __builtin_fmaxf(am, dpp_xor<2>(am));
-      const int32_t X = mx_exponent(am);
-      uint32_t packed = e2m1_pair<0>(0u, v[i][0], v[i][1], X);
-      packed = e2m1_pair<1>(packed, v[i][2], v[i][3], X);
-      packed = e2m1_pair<2>(packed, v[i][4], v[i][5], X);
-      packed = e2m1_pair<3>(packed, v[i][6], v[i][7], X);
+      int32_t X;
+      const uint32_t packed = mxfp4_x8(v[i], X);
       const int64_t col = base + 8 * lane;
       *(uint32_t*)((uint8_t*)A.xq + row * (A.K / 2) + col / 2) = packed;
       if ((lane & 3) == 0) A.mxs[row * (A.K / 32) + col / 32] = (uint8_t)(X + 127);
@@ -858,17 +849,23 @@ __global__ __launch_bounds__(256) void hq_act_prep_kernel(hq_actprep_args A) {
     for (int64_t base = 0; base < A.K; base += 1024) {
       const int64_t col = base + (int64_t)tid * 4;
       const bool in = col < A.K;  // whole 32-blocks are in or out (K is a multiple of 512)
-      float q[4], am = 0.0f;
+      float q[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        q[i] = in ? ybuf[col + i] : 0.0f;
-        am = __builtin_fmaxf(am, __builtin_fabsf(q[i]));
+      for (int i = 0; i < 4; ++i) q[i] = in ? ybuf[col + i] : 0.0f;
+      int32_t X;
+      auto cast = [&](float am) {
+        am = __builtin_fmaxf(am, __shfl_xor(am, 1, 64));
+        am = __builtin_fmaxf(am, __shfl_xor(am, 2, 64));
+        am = __builtin_fmaxf(am, __shfl_xor(am, 4, 64));
+        X = mx_exponent(am);
+        return e2m1_pair<1>(e2m1_pair<0>(0u, q[0], q[1], X), q[2], q[3], X);
+      };
+      const float am0 = amax_or_nan<4>(q);
+      uint32_t packed = cast(am0);
+      if (__builtin_expect(__ballot(am0 != am0) != 0ull, 0)) {
+        e2m1_drop_nan<4>(q);
+        packed = cast(amax_or_nan<4>(q));
       }
-      am = __builtin_fmaxf(am, __shfl_xor(am, 1, 64));
-      am = __builtin_fmaxf(am, __shfl_xor(am, 2, 64));
-      am = __builtin_fmaxf(am, __shfl_xor(am, 4, 64));
-      const int32_t X = mx_exponent(am);
-      const uint32_t packed = e2m1_pair<1>(e2m1_pair<0>(0u, q[0], q[1], X), q[2], q[3], X);
       if (in) {
         *(uint16_t*)((uint8_t*)A.xq + row * (A.K / 2) + col / 2) = (uint16_t)packed;
         if ((tid & 7) == 0) A.mxs[row * (A.K / 32) + col / 32] = (uint8_t)(X + 127);
