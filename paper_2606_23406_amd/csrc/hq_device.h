@@ -1363,7 +1363,7 @@ __device__ __forceinline__ void store_slot(uint32_t a, uint32_t v, int32_t n) {
       "s_mov_b64 exec, %0"
       : "=&s"(saved)
       : "v"(a), "v"(v), "v"(n), "n"(N), "n"(4 * N)
-      : "vcc", "memory");
+      : "vcc", "scc", "memory");
 }
 
 // The 8 symbols of group `grp` (0 .. 63, a permutation of the lanes) of a
