@@ -217,10 +217,11 @@ __device__ __forceinline__ void gemm_rescale(const typename C::acc_t& p, float g
   for (int r = R0; r < R1; ++r) acc[r] = __builtin_fmaf((float)p[r], g, acc[r]);
 }
 
-__device__ __forceinline__ uint32_t gemm_bf16(float v) {
-  uint32_t r;
-  asm("v_cvt_pk_bf16_f32 %0, %1, %1" : "=v"(r) : "v"(v));
-  return r;
+// fp32 -> bf16, round to nearest even (v_cvt_pk_bf16_f32).  Not by inline
+// assembly: the value may be a matrix core's result, and the compiler does not
+// look into assembly for the wait states before it.
+__device__ __forceinline__ uint16_t gemm_bf16(float v) {
+  return __builtin_bit_cast(uint16_t, (__bf16)v);
 }
 
 // One 32-row by 64-column slab of a wave's outputs: into the wave's LDS
@@ -240,7 +241,7 @@ __device__ __forceinline__ void gemm_store_slab(const hq_gemm_args& A, int8_t* t
     for (int r = 0; r < 16; ++r) {
       int8_t* const p = tile + (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * RS + (b * 32 + (lane & 31)) * ES;
       if constexpr (BF16)
-        *(uint16_t*)p = (uint16_t)gemm_bf16(v[b][r]);
+        *(uint16_t*)p = gemm_bf16(v[b][r]);
       else
         *(float*)p = v[b][r];
     }

@@ -34,3 +34,12 @@ def test_scalar_condition_code_is_declared():
             seen += 1
             assert re.search(r'"scc"', body), (path, writes)
     assert seen > 0
+
+
+def test_gemm_assembly_reads_no_vector_registers():
+    """The GEMM's values come straight from the matrix cores: its inline assembly is waits and
+    barriers only."""
+    bodies = [body for path, body in asm_statements() if path == "hq_gemm.hip"]
+    assert bodies
+    for body in bodies:
+        assert not re.search(r'"[=+&]*[va]"\s*\(', body), body
