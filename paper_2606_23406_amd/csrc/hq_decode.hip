@@ -8,77 +8,6 @@
 
 namespace {
 
-// ------------------------------------------------------------ transform on the matrix cores
-// A plain weight plan's codes are integers, so its inverse transform is exact
-// in any order, and 32 of a tile's 128 points fit one matrix-core step: with
-// lane l holding block (l & 3) | (l >> 4) << 2 of tile (l >> 2) & 3, the lane's 8
-// coordinates and the lanes l, l + 16, l + 32, l + 48 make the K index
-// 8 (l / 16) + j of v_mfma_f32_16x16x32_f16's B operand, column l % 16.  The A
-// operand is H32 with its rows in the order that returns every sum to the
-// lane layout it came from (row 4 g' + r of product h is coordinate 4 h + r
-// of lane group g'), and the blocks' two low index bits remain, as two DPP
-// butterflies.  The codes enter as 1536 + c in fp16 (exact for |c| < 512: one
-// shift-and-add per pair); the bias shows only in the all-ones row, where the
-// C operand takes 32 * 1536 away.  All values are integers below 2^24: exact.
-// Against the seven-stage transform on the VALU (integer conversions, 24 adds,
-// 32 cross-lane multiply-adds) it leaves 16 cross-lane ones.
-typedef _Float16 v8h_t __attribute__((ext_vector_type(8)));
-typedef float v4f_t __attribute__((ext_vector_type(4)));
-typedef uint32_t v4u_t __attribute__((ext_vector_type(4)));
-constexpr uint32_t kCodeBias = 0x66006600u;  // 1536 in each fp16 half
-
-struct MfmaRht {
-  v4u_t a0, a1;  // the two products' A rows, fp16 +-1 pairs
-  v4f_t c0;      // C of product 0
-  float f[2];    // stage signs of the lane's block bits 0 and 1
-  uint32_t sigma;
-  __device__ __forceinline__ explicit MfmaRht(int lane) {
-    const uint32_t r = lane & 3, go = (lane >> 2) & 3, gi = (uint32_t)lane >> 4;
-    const uint32_t s = __popc(gi & go) & 1u;
-    uint32_t w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      // K values j = 2 i and 2 i + 1: sign (-1)^(popc(j & r) + s)
-      const uint32_t lo = (__popc((2 * i) & r) + s) & 1u, hi = (__popc((2 * i + 1) & r) + s) & 1u;
-      w[i] = 0x3C003C00u ^ (lo << 15) ^ (hi << 31);
-    }
-    a0 = (v4u_t){w[0], w[1], w[2], w[3]};
-    a1 = (v4u_t){w[0], w[1], w[2] ^ 0x80008000u, w[3] ^ 0x80008000u};  // coordinate bit 2 set
-    c0 = (v4f_t){lane < 16 ? -32.0f * 1536.0f : 0.0f, 0.0f, 0.0f, 0.0f};
-    f[0] = (lane & 1) ? -1.0f : 1.0f;
-    f[1] = (lane & 2) ? -1.0f : 1.0f;
-    sigma = (uint32_t)(__popc((uint32_t)lane & 3u) & 1) << 31;
-    // kept in registers for the whole kernel
-    asm volatile("" : "+v"(a0), "+v"(a1), "+v"(c0), "+v"(f[0]), "+v"(f[1]), "+v"(sigma));
-  }
-  // y = sigma * (H c) for |c| < 512, c given as biased fp16 pairs.
-  __device__ __forceinline__ void small(const uint32_t (&pair)[4], float* y) const {
-    const v8h_t b = __builtin_bit_cast(v8h_t, (v4u_t){pair[0], pair[1], pair[2], pair[3]});
-    const v4f_t lo = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h_t, a0), b, c0, 0, 0, 0);
-    const v4f_t hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h_t, a1), b, (v4f_t){}, 0, 0, 0);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      y[j] = lo[j];
-      y[4 + j] = hi[j];
-    }
-    stages(y);
-  }
-  // The same for any code, on the VALU.
-  __device__ __forceinline__ void any(float* y, int lane) const {
-    fwht8_inlane(y);
-    const float s4 = (lane & 16) ? -1.0f : 1.0f, s5 = (lane & 32) ? -1.0f : 1.0f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) y[j] = __builtin_fmaf(y[j], s4, swz_xor16(y[j]));
-#pragma unroll
-    for (int j = 0; j < 8; ++j) y[j] = __builtin_fmaf(y[j], s5, lane_xor32(y[j]));
-    stages(y);
-  }
-  __device__ __forceinline__ void stages(float* y) const {
-    HQ_FMAC_DPP8("quad_perm:[1,0,3,2]", y, f[0]);
-    HQ_FMAC_DPP8("quad_perm:[2,3,0,1]", y, f[1]);
-  }
-};
-
 // 16 output bytes that this kernel does not read again.
 __device__ __forceinline__ void store_stream(void* p, uint4 v) {
   __builtin_nontemporal_store((v4u_t){v.x, v.y, v.z, v.w}, (v4u_t*)p);
@@ -535,7 +464,6 @@ __global__ __launch_bounds__(256) void hq_decode_tiled_kernel(hq_decode_args A) 
 //     store.
 // The contraction sums in the matrix cores' order, so the output equals
 // the oracle's left-to-right fp32 sums to rounding, not bit for bit.
-typedef float v4f_t __attribute__((ext_vector_type(4)));
 constexpr int kQjlRow = 130;            // floats per tile row of Y
 constexpr int kQjlTiles = 64;           // tiles per workgroup pass (16 sub-streams)
 
@@ -674,19 +602,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void h
   }
 }
 
+// (256, 2): at most 256 registers, so that the matrix cores' results go to
+// plain ones (otherwise four copies to and eight from accumulation registers
+// per sub-stream).
 template <int LAT, int MODE, bool KV>
-__global__ __launch_bounds__(256) void hq_decode_kernel(hq_decode_args A) {
+__global__ __launch_bounds__(256, 2) void hq_decode_kernel(hq_decode_args A) {
   decode_wg<LAT, MODE, KV>(A, blockIdx.x);
 }
 
 // Single matrices of fewer than HQ_DEC_SMALL sub-streams: one per wave.
 template <int LAT, int MODE, bool KV>
-__global__ __launch_bounds__(256) void hq_decode_small_kernel(hq_decode_args A) {
+__global__ __launch_bounds__(256, 2) void hq_decode_small_kernel(hq_decode_args A) {
   decode_wg<LAT, MODE, KV, 1>(A, blockIdx.x);
 }
 
 template <int LAT, int MODE, bool KV>
-__global__ __launch_bounds__(256) void hq_decode_group_kernel(hq_decode_group_args G) {
+__global__ __launch_bounds__(256, 2) void hq_decode_group_kernel(hq_decode_group_args G) {
   int mi = 0;
   for (int i = 1; i < G.count; ++i) mi = blockIdx.x >= G.wg_begin[i] ? i : mi;
   decode_wg<LAT, MODE, KV>(G.m[mi], blockIdx.x - G.wg_begin[mi]);

@@ -2,6 +2,7 @@
 import glob
 import os
 import re
+import subprocess
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2606_23406_amd", "csrc")
 
@@ -34,6 +35,64 @@ def test_scalar_condition_code_is_declared():
             seen += 1
             assert re.search(r'"scc"', body), (path, writes)
     assert seen > 0
+
+
+PROBE = r"""
+#include "hq_device.h"
+__global__ __launch_bounds__(256, 2) void by_asm(const uint32_t* c, float* o) {
+  const MfmaRht m(threadIdx.x & 63);
+  const uint32_t p[4] = {c[4 * threadIdx.x], c[4 * threadIdx.x + 1], c[4 * threadIdx.x + 2], c[4 * threadIdx.x + 3]};
+  float y[8];
+  m.small(p, y);
+  for (int j = 0; j < 8; ++j) o[8 * threadIdx.x + j] = y[j];
+}
+__global__ __launch_bounds__(256, 2) void by_compiler(const v8h_t* c, float* o) {
+  const v4f_t r = __builtin_amdgcn_mfma_f32_16x16x32_f16(c[threadIdx.x], c[threadIdx.x + 64], (v4f_t){}, 0, 0, 0);
+  o[threadIdx.x] = r[0] * 3.0f;
+}
+"""
+
+
+def wait_states(body):
+    """Wait states between each matrix instruction and the first instruction, inline or not, that has
+    one of its result registers among its operands."""
+    pending, now, out = [], 0, []
+    for line in body.split("\n"):
+        t = line.split(";")[0].strip()
+        if not t or t.endswith(":") or t.startswith("."):
+            continue
+        if t.startswith("s_nop"):
+            now += int(t.split()[1]) + 1
+            continue
+        regs = set()
+        for b, lo, hi, b1, r1 in re.findall(r"\b([va])\[(\d+):(\d+)\]|\b([va])(\d+)\b", t):
+            regs |= {(b1, int(r1))} if b1 else {(b, i) for i in range(int(lo), int(hi) + 1)}
+        for at, res in [p for p in pending if p[1] & regs]:
+            out.append(now - at)
+            pending.remove((at, res))
+        now += 1
+        if t.startswith("v_mfma"):
+            b, lo, hi = re.match(r"\S+\s+([va])\[(\d+):(\d+)\]", t).groups()
+            pending.append((now, {(b, i) for i in range(int(lo), int(hi) + 1)}))
+    assert not pending
+    return out
+
+
+def test_matrix_results_wait_before_inline_assembly(tmp_path):
+    """The transform's inline assembly reads matrix-core results no sooner than the compiler lets its
+    own instructions read them, also where they are not copied between register files first."""
+    from paper_2606_23406_amd import build
+    src, s = tmp_path / "probe.hip", tmp_path / "probe.s"
+    src.write_text(PROBE)
+    flags = [f for f in build.FLAGS if f not in ("-fPIC", "-Wall")]
+    subprocess.run([build.HIPCC] + flags + ["-w", "-I", CSRC, "-S", "--offload-device-only", "-o", str(s), str(src)],
+                   check=True, timeout=120)
+    text = s.read_text()
+    body = {k: re.search(r"\n_Z\d+%s\w*:(.*?)s_endpgm" % k, text, re.S).group(1) for k in ("by_asm", "by_compiler")}
+    (need,) = wait_states(body["by_compiler"])
+    got = wait_states(body["by_asm"])
+    assert need >= 4 and len(got) == 2
+    assert min(got) >= need, (got, need)
 
 
 def test_gemm_assembly_reads_no_vector_registers():
