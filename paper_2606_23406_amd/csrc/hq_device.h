@@ -122,12 +122,10 @@ __device__ __forceinline__ uint32_t lshl_or(uint32_t a, uint32_t sh, uint32_t c)
   asm("v_lshl_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(sh), "v"(c));
   return r;
 }
-// (a << sh) | c with a wave-uniform shift held in a scalar register
-__device__ __forceinline__ uint32_t lshl_or_s(uint32_t a, uint32_t sh, uint32_t c) {
-  uint32_t r;
-  asm("v_lshl_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(sh), "v"(c));
-  return r;
-}
+// (a << sh) | c with a wave-uniform shift below 32: the compiler's own, which
+// may come right behind the instruction that writes the shift's scalar register
+// (inline assembly would need its two wait states)
+__device__ __forceinline__ uint32_t lshl_or_s(uint32_t a, uint32_t sh, uint32_t c) { return (a << sh) | c; }
 __device__ __forceinline__ uint32_t bit_or(uint32_t sh, uint32_t c) {
   uint32_t r;
   asm("v_lshl_or_b32 %0, 1, %1, %2" : "=v"(r) : "v"(sh), "v"(c));
@@ -1497,8 +1495,10 @@ __device__ __forceinline__ unsigned long long decode_symbols(const hq_decode_arg
       pos = grp != 0u ? pos : R;
       const uint32_t win = bits32_at(buf, pos);
       if (__ballot(__popc(win) < 8) == 0ull) {
+        // (__umul24 becomes the slow 32-bit product; the two wait states a vector
+        // instruction needs behind one that wrote its scalar operand stand here)
         uint32_t rpos;
-        asm("v_mul_u32_u24 %0, %1, %2" : "=v"(rpos) : "v"(grp), "s"(lrem));
+        asm("s_nop 1\n\tv_mul_u32_u24 %0, %1, %2" : "=v"(rpos) : "v"(grp), "s"(lrem));
         const uint32_t acc = bits32_at(buf, rpos);
         uint32_t sh = 0;
 #pragma unroll

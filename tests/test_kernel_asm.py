@@ -21,7 +21,7 @@ def asm_statements():
                 quoted ^= c == '"' and text[i - 1] != "\\"
                 depth += 0 if quoted else (c == "(") - (c == ")")
                 i += 1
-            yield os.path.basename(path), text[m.end():i - 1]
+            yield os.path.basename(path), text[m.end():i - 1].replace("\\n", " ").replace("\\t", " ")
 
 
 def test_scalar_condition_code_is_declared():
@@ -102,3 +102,17 @@ def test_gemm_assembly_reads_no_vector_registers():
     assert bodies
     for body in bodies:
         assert not re.search(r'"[=+&]*[va]"\s*\(', body), body
+
+
+def test_scalar_operands_wait():
+    """A vector instruction in inline assembly with a scalar register operand has the two wait states
+    in front that it needs behind a vector instruction that wrote the register; carry operands need
+    none."""
+    seen = 0
+    for path, body in asm_statements():
+        ops = re.findall(r"\b(v_\w+)", body)
+        if not ops or not re.search(r'"s"\s*\(', body) or all(o.startswith(("v_addc", "v_subb")) for o in ops):
+            continue
+        seen += 1
+        assert re.match(r'\s*"s_nop [1-9]', body), (path, body)
+    assert seen > 0
