@@ -624,18 +624,6 @@ hq_status hq_decode_gemv(hq_plan_t p, const hq_stream* s, int64_t row0, int64_t 
   return hip_status(hq_launch_decode_gemv(p, a, x, xt, (float*)workspace, y, yt, stream));
 }
 
-// Tokens per wave of the fused attention: about 16384 waves over the call
-// (several rounds of the waves that fit at once, so the last round is a
-// small share), from 4 to 1024 tokens each.  A wave takes about 2.5 us a
-// token in turn, so a small call wants few tokens per wave: 3 sequences of
-// 1500 tokens take 76 us at 16 a wave, 56 at 8, 44 at 4 and 43 at 2, one of 300
-// 72, 45, 31 and 25, but one of 8192 78, 62, 65 and 84 (more splits to
-// combine).
-static int64_t attn_chunk(const hq_plan_s* k, int64_t batch, int64_t max_tokens) {
-  const int64_t work = batch * k->spr * max_tokens;
-  return std::min<int64_t>(1024, std::max<int64_t>(4, (work + 16383) / 16384));
-}
-
 static int64_t attn_splits(int64_t max_tokens, int64_t chunk) {
   const int64_t per = HQ_WAVES_PER_WG * chunk;
   return (max_tokens + per - 1) / per;
@@ -703,7 +691,7 @@ hq_status hq_decode_attention(hq_plan_t pk, const hq_stream* k, hq_plan_t pv, co
   if (!k->payload || !k->offsets || !k->kparam || !k->norms || !v->payload || !v->offsets ||
       !v->kparam || !v->norms)
     return HQ_ERR_INVALID_ARG;
-  const int64_t chunk = attn_chunk(pk, batch, max_tokens);
+  const int64_t chunk = hq_attn_chunk(pk->spr, batch, max_tokens);
   const int64_t nx = attn_splits(max_tokens, chunk);
   if (batch * pk->spr * nx > 0x7FFFFFFF || batch * heads_q > 0x7FFFFFFF) return HQ_ERR_UNSUPPORTED;
   hq_attn_args a;

@@ -44,6 +44,23 @@ struct hq_plan_s {
   int device;
 };
 
+// Tokens per wave of the fused attention over rows of `spr` sub-streams: about
+// 16384 waves over the call (several rounds of the waves that fit at once, so
+// the last round is a small share), at most 1024 tokens each and at least 4 to
+// 16.  A wave takes about 2.5 us a token in turn, so a small call wants few
+// tokens per wave; but the combine, one workgroup a query head, walks a head's
+// splits (one per four waves) in turn, about 0.05 us each, so the least number
+// grows with the tokens, 512 splits a head at most until it is 16.  At 16, 8 and
+// 4 tokens a wave 3 sequences of 1500 take 76, 56 and 44 us and one of 300 72, 45
+// and 31; one of 16384 takes 87 us at this rule's 8 and 106 at 4, one of 32768
+// 140 at its 16 and 195 at 4 (8 KV heads, 4 query heads each).
+static inline int64_t hq_attn_chunk(int64_t spr, int64_t batch, int64_t max_tokens) {
+  const int64_t work = batch * spr * max_tokens, by_combine = (max_tokens + 2047) / 2048;
+  const int64_t least = by_combine < 4 ? 4 : by_combine > 16 ? 16 : by_combine;
+  const int64_t even = (work + 16383) / 16384;
+  return even < least ? least : even > 1024 ? 1024 : even;
+}
+
 // Arguments of the encode kernel (passed by value).
 struct hq_encode_args {
   const void* x;
