@@ -14,7 +14,7 @@ LIB = os.path.join(HERE, "libhq.so")
 SOURCES = [os.path.join(CSRC, f) for f in ("hq_encode.hip", "hq_decode.hip", "hq_fused.hip", "hq_gemm.hip",
                                           "hq_host.cpp")]
 DEPS = SOURCES + [os.path.join(CSRC, "hq_internal.h"), os.path.join(CSRC, "hq_device.h"),
-                  os.path.join(CSRC, "calib_table.inc"),
+                  os.path.join(CSRC, "hq_lds.h"), os.path.join(CSRC, "calib_table.inc"),
                   os.path.join(os.path.dirname(HERE), "include", "hq.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -3,6 +3,7 @@
 #include <type_traits>
 
 #include "hq_device.h"
+#include "hq_lds.h"
 
 #pragma clang fp contract(off)
 
@@ -626,10 +627,10 @@ __global__ __launch_bounds__(256, 2) void hq_decode_group_kernel(hq_decode_group
 // One decode launch: a single matrix (hq_decode_args) or a group.
 template <int LAT, int MODE, bool KV, typename Args>
 void launch_decode_kernel(const Args& a, uint32_t nwg, size_t lds, hipStream_t st) {
-  static size_t granted = 0;
-  allow_lds(sizeof(Args) == sizeof(hq_decode_args) ? (const void*)hq_decode_kernel<LAT, MODE, KV>
-                                                   : (const void*)hq_decode_group_kernel<LAT, MODE, KV>,
-            lds, granted);
+  static hq_lds_granted granted;
+  hq_allow_lds(sizeof(Args) == sizeof(hq_decode_args) ? (const void*)hq_decode_kernel<LAT, MODE, KV>
+                                                      : (const void*)hq_decode_group_kernel<LAT, MODE, KV>,
+               lds, granted);
   if constexpr (sizeof(Args) == sizeof(hq_decode_args))
     hipLaunchKernelGGL((hq_decode_kernel<LAT, MODE, KV>), dim3(nwg), dim3(256), lds, st, a);
   else
@@ -659,12 +660,12 @@ int launch_decode_lat(const Args& a, uint32_t nwg, uint32_t lds_words, int mode,
 template <int LAT>
 int launch_decode_tiled(const hq_decode_args& a, uint32_t nwg, int mode, hipStream_t st) {
   const size_t lds = (size_t)(a.lds_words + 66) * HQ_WAVES_PER_WG * sizeof(uint32_t);
-  static size_t granted_0 = 0, granted_1 = 0;
+  static hq_lds_granted granted_0, granted_1;
   if (mode == 0) {
-    allow_lds((const void*)hq_decode_tiled_kernel<LAT, 0>, lds, granted_0);
+    hq_allow_lds((const void*)hq_decode_tiled_kernel<LAT, 0>, lds, granted_0);
     hipLaunchKernelGGL((hq_decode_tiled_kernel<LAT, 0>), dim3(nwg), dim3(256), lds, st, a);
   } else {
-    allow_lds((const void*)hq_decode_tiled_kernel<LAT, 1>, lds, granted_1);
+    hq_allow_lds((const void*)hq_decode_tiled_kernel<LAT, 1>, lds, granted_1);
     hipLaunchKernelGGL((hq_decode_tiled_kernel<LAT, 1>), dim3(nwg), dim3(256), lds, st, a);
   }
   return (int)hipGetLastError();
@@ -686,12 +687,12 @@ int launch_decode_qjl(const hq_decode_args& a, int mode, hipStream_t st) {
   const uint32_t nwg = (uint32_t)std::min<int64_t>(ngroups, 2048);
   const size_t lds = (size_t)(a.lds_words + 66) * HQ_WAVES_PER_WG * sizeof(uint32_t) +
                      (size_t)kQjlTiles * kQjlRow * sizeof(float);
-  static size_t granted0 = 0, granted1 = 0;
+  static hq_lds_granted granted0, granted1;
   if (mode == 0) {
-    allow_lds((const void*)hq_decode_qjl_kernel<LAT, 0>, lds, granted0);
+    hq_allow_lds((const void*)hq_decode_qjl_kernel<LAT, 0>, lds, granted0);
     hipLaunchKernelGGL((hq_decode_qjl_kernel<LAT, 0>), dim3(nwg), dim3(256), lds, st, a);
   } else {
-    allow_lds((const void*)hq_decode_qjl_kernel<LAT, 1>, lds, granted1);
+    hq_allow_lds((const void*)hq_decode_qjl_kernel<LAT, 1>, lds, granted1);
     hipLaunchKernelGGL((hq_decode_qjl_kernel<LAT, 1>), dim3(nwg), dim3(256), lds, st, a);
   }
   return (int)hipGetLastError();
@@ -704,9 +705,9 @@ template <int LAT>
 int launch_decode_small(const hq_decode_args& a, int mode, bool kv, hipStream_t st) {
   const uint32_t nwg = (uint32_t)((a.nsub + HQ_WAVES_PER_WG - 1) / HQ_WAVES_PER_WG);
   const size_t lds = (size_t)(a.lds_words + 66) * HQ_WAVES_PER_WG * sizeof(uint32_t);
-  static size_t granted[4] = {0, 0, 0, 0};
+  static hq_lds_granted granted[4];
 #define HQ_SMALL_CASE(M, K, I)                                                             \
-  allow_lds((const void*)hq_decode_small_kernel<LAT, M, K>, lds, granted[I]);              \
+  hq_allow_lds((const void*)hq_decode_small_kernel<LAT, M, K>, lds, granted[I]);           \
   hipLaunchKernelGGL((hq_decode_small_kernel<LAT, M, K>), dim3(nwg), dim3(256), lds, st, a)
   if (mode == 0) {
     if (kv) { HQ_SMALL_CASE(0, true, 0); } else { HQ_SMALL_CASE(0, false, 1); }

@@ -1522,15 +1522,6 @@ __device__ __forceinline__ unsigned long long decode_symbols(const hq_decode_arg
   return __ballot(!decode_symbols_general<LAT>(h.ok, Wl, R, k0, k1, lane, grp, known, pos, buf, starts, sym));
 }
 
-// Dynamic LDS above 64 KB needs a per-kernel opt-in, a costly runtime call:
-// made when a launch needs more than the kernel's largest opt-in so far.
-inline void allow_lds(const void* kernel, size_t bytes, size_t& granted) {
-  if (bytes > 65536 && bytes > granted &&
-      hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) ==
-          hipSuccess)
-    granted = bytes;
-}
-
 inline bool kv_variant(const hq_plan_s* p) { return p->rotation || p->dither || p->norm_fp16; }
 
 }  // namespace

@@ -2,6 +2,7 @@
 #include <mutex>
 
 #include "hq_device.h"
+#include "hq_lds.h"
 
 #pragma clang fp contract(off)
 
@@ -984,8 +985,8 @@ int launch_encode_lat(const Args& a, const hq_rice_thr& t, uint32_t nwg, uint32_
 template <int LAT, int XT, int MB>
 int launch_encode_tiled_mb(const hq_encode_args& a, const hq_rice_thr& t, hipStream_t st) {
   const size_t lds = (size_t)(a.lds_words + 2) * HQ_ENC_SUBS_PER_WG * sizeof(uint32_t);
-  static size_t granted = 0;
-  allow_lds((const void*)hq_encode_tiled_kernel<LAT, XT, MB>, lds, granted);
+  static hq_lds_granted granted;
+  hq_allow_lds((const void*)hq_encode_tiled_kernel<LAT, XT, MB>, lds, granted);
   hipLaunchKernelGGL((hq_encode_tiled_kernel<LAT, XT, MB>), dim3(a.nwg), dim3(64 * HQ_ENC_WAVES), lds, st,
                      a, t);
   return (int)hipGetLastError();

@@ -18,6 +18,7 @@
 #include <stdint.h>
 
 #include "hq_internal.h"
+#include "hq_lds.h"
 
 #pragma clang fp contract(off)
 
@@ -502,13 +503,8 @@ __global__ __launch_bounds__(C::W * 64, C::W <= 4 ? 1 : 2) void hq_gemm_kernel(h
 
 template <class C>
 int gemm_launch(const hq_gemm_args& a, hipStream_t st) {
-  static bool lds_set = false;  // more than 64 KB of dynamic LDS needs an opt-in
-  if (!lds_set) {
-    const hipError_t e = hipFuncSetAttribute((const void*)hq_gemm_kernel<C>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
-    if (e != hipSuccess) return (int)e;
-    lds_set = true;
-  }
+  static hq_lds_granted granted;
+  if (const int e = hq_allow_lds((const void*)hq_gemm_kernel<C>, C::LDS, granted)) return e;
   const int64_t wgs = ((a.M + C::BM - 1) / C::BM) * ((a.N + C::BN - 1) / C::BN);
   hipLaunchKernelGGL(hq_gemm_kernel<C>, dim3((uint32_t)wgs), dim3(C::W * 64), C::LDS, st, a);
   return (int)hipGetLastError();
