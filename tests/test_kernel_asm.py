@@ -95,6 +95,18 @@ def test_matrix_results_wait_before_inline_assembly(tmp_path):
     assert min(got) >= need, (got, need)
 
 
+def test_gemm_keeps_products_in_plain_registers(tmp_path):
+    """No GEMM kernel copies its products between register files or spills them."""
+    from paper_2606_23406_amd import build
+    s = tmp_path / "gemm.s"
+    flags = [f for f in build.FLAGS if f not in ("-fPIC", "-Wall")]
+    subprocess.run([build.HIPCC] + flags + ["-w", "-S", "--offload-device-only", "-o", str(s),
+                                            os.path.join(CSRC, "hq_gemm.hip")], check=True, timeout=300)
+    text = s.read_text()
+    assert text.count("v_mfma") > 100
+    assert "v_accvgpr" not in text and not re.search(r"scratch_(load|store)", text)
+
+
 def test_gemm_assembly_reads_no_vector_registers():
     """The GEMM's values come straight from the matrix cores: its inline assembly is waits and
     barriers only."""
