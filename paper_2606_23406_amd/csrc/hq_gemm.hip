@@ -515,32 +515,20 @@ int gemm_launch(const hq_gemm_args& a, hipStream_t st) {
   return (int)hipGetLastError();
 }
 
-// The workgroup tile.  A product's time goes with its rounds of one workgroup
-// per CU (256 CUs) times a round's time; measured in microseconds at K = 4096,
-// int8 / E4M3 / MXFP4 (MI355X):
-//   256 x 256  79 / 67 / 41     128 x 128  29 / 26 / 15 (four-stage ring)
-// so a round of the large tile, which fetches and reads half as many operand
-// bytes per product, counts as 11 and one of the small tile as 4.  Factor
-// tiles of several stages (LONG) keep their partial sums next to the
-// accumulators: 256 x 128, 38 / 35 a round, counts as 8 against 5 (23 / 21).
-// Below 512 tiles of 64 x 64, one wave each and two on a CU, a product takes
-// one short round of those (16 x 4096: 26 / 22 / 10 against 28 / 26 / 11).
 template <int MODE>
 int gemm_dispatch(const hq_gemm_args& a, hipStream_t st) {
-  auto tiles = [&](int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-  auto rounds = [&](int bm, int bn) { return (tiles(bm, bn) + 255) / 256; };
-  const bool tiny = tiles(64, 64) <= 512;
+  const bool lng = MODE != 2 && a.tile > HQ_TILE;
+  const hq_gemm_tile t = hq_gemm_tile_of(MODE, lng, a.M, a.N);
   if constexpr (MODE != 2) {
-    if (a.tile > HQ_TILE) {
-      if (tiny) return gemm_launch<GemmCfg<MODE, 64, 64, 1, 1, true, 4>>(a, st);
-      if (5 * rounds(128, 128) < 8 * rounds(256, 128))
-        return gemm_launch<GemmCfg<MODE, 128, 128, 2, 2, true, 4>>(a, st);
+    if (lng) {
+      if (t == HQ_GEMM_64x64) return gemm_launch<GemmCfg<MODE, 64, 64, 1, 1, true, 4>>(a, st);
+      if (t == HQ_GEMM_128x128) return gemm_launch<GemmCfg<MODE, 128, 128, 2, 2, true, 4>>(a, st);
       return gemm_launch<GemmCfg<MODE, 256, 128, 4, 2, true, 3>>(a, st);
     }
   }
-  if (tiny) return gemm_launch<GemmCfg<MODE, 64, 64, 1, 1, false, 4>>(a, st);
-  if (4 * rounds(128, 128) < 11 * rounds(256, 256))
-    return gemm_launch<GemmCfg<MODE, 128, 128, 2, 2, false, 4>>(a, st);
+  if (t == HQ_GEMM_64x64) return gemm_launch<GemmCfg<MODE, 64, 64, 1, 1, false, 4>>(a, st);
+  if (t == HQ_GEMM_128x128) return gemm_launch<GemmCfg<MODE, 128, 128, 2, 2, false, 4>>(a, st);
+  if (t == HQ_GEMM_256x128) return gemm_launch<GemmCfg<MODE, 256, 128, 4, 2, false, 3>>(a, st);
   return gemm_launch<GemmCfg<MODE, 256, 256, 2, 4, false, 2>>(a, st);
 }
 

@@ -61,6 +61,33 @@ static inline int64_t hq_attn_chunk(int64_t spr, int64_t batch, int64_t max_toke
   return even < least ? least : even > 1024 ? 1024 : even;
 }
 
+// The workgroup tile of a block-scaled product of M x N outputs (mode 0 int8, 1
+// E4M3, 2 MXFP4).  Its time goes with its rounds of one workgroup per CU (256
+// CUs) times a round's time; a full round takes, in microseconds at K = 4096,
+// int8 / E4M3 / MXFP4:
+//   128 x 128  28 / 24 / 15.7    256 x 128  44 / 37.5 / 26    256 x 256  75 / 64 / 39
+// (the larger the tile, the fewer operand bytes per product).  They count as 8,
+// 12 (MXFP4: 13) and 19, a tie going to the larger tile: a little below those
+// ratios for the larger ones, whose partly filled last round runs faster.  Over M
+// 32 .. 8192, N 500 .. 14336 and K 1024 .. 14336 the rule's tile takes 0.2 % more than the
+// best on average.  500 x 14336 x 4096 in E4M3: 36.7 us in one round of 256 x 128
+// tiles, 46.7 in two of 128 x 128, 50.4 in one of 256 x 256.  `lng`, int8 and E4M3 factor
+// tiles of several stages, which keep their partial sums next to the
+// accumulators: 128 x 128 (23 / 22) and 256 x 128 (38 / 35) only, 8 and 12 as well.  Up
+// to 512 tiles of 64 x 64, one wave each and two on a CU, are one short round and as
+// fast as the others' (32 x 4096 x 4096: 22.7 / 19.5 / 11.4 us against 23.7 / 19.5 / 11.4 in
+// 128 x 128); two rounds of them take 1.4 to 1.8 times the larger tiles' one.
+enum hq_gemm_tile { HQ_GEMM_64x64, HQ_GEMM_128x128, HQ_GEMM_256x128, HQ_GEMM_256x256 };
+static inline hq_gemm_tile hq_gemm_tile_of(int mode, bool lng, int64_t M, int64_t N) {
+  auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  auto rounds = [&](int64_t bm, int64_t bn) { return (tiles(bm, bn) + 255) / 256; };
+  if (tiles(64, 64) <= 512) return HQ_GEMM_64x64;
+  const int64_t c128 = 8 * rounds(128, 128), c256 = (mode == 2 ? 13 : 12) * rounds(256, 128);
+  const hq_gemm_tile t = c128 < c256 ? HQ_GEMM_128x128 : HQ_GEMM_256x128;
+  if (lng) return t;
+  return 19 * rounds(256, 256) <= (c128 < c256 ? c128 : c256) ? HQ_GEMM_256x256 : t;
+}
+
 // Arguments of the encode kernel (passed by value).
 struct hq_encode_args {
   const void* x;

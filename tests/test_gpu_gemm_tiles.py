@@ -1,8 +1,9 @@
 """The block-scaled GEMMs in every workgroup tile the dispatch picks, against a 64-bit product.
 
-Sizes: 64 x 64 tiles up to 512 of them, then 128 x 128, then 256 x 256 (256 x 128 for factor tiles
-longer than 128) once those take fewer rounds of the chip; edges off every tile in both directions,
-and the shortest K (fewer stages than the LDS ring holds).
+Sizes: 64 x 64 tiles up to 512 of them, then 128 x 128, 256 x 128 or 256 x 256 (the last not for factor
+tiles longer than 128), whichever take the fewest weighted rounds of the chip; edges off every tile in
+both directions, the shortest K (no more stages than the LDS ring holds) and a K that fills the ring
+again at least twice, MXFP4's stages of 256 included.
 """
 import pytest
 import torch
@@ -54,9 +55,10 @@ def _operands(cast, M, N, K, tile):
                                        ("mxfp4", 128)])
 @pytest.mark.parametrize("M,N,K", [
     (1, 1, 512), (63, 130, 512), (65, 64, 2560),          # 64 x 64
-    (1100, 2050, 1024),                                   # 128 x 128
+    (1100, 2050, 1024), (1100, 2050, 2560),               # 128 x 128
+    (500, 11000, 512), (500, 11000, 2560),                # 256 x 128
     (2000, 3900, 1024),                                   # long factor tiles: 256 x 128
-    (3000, 3001, 512),                                    # 256 x 256
+    (3000, 3001, 512), (3000, 3001, 1536),                # 256 x 256
 ])
 def test_gemm_workgroup_tiles(hq, cast, tile, M, N, K):
     print(f"[parity] gemm {cast} tile {tile} {M}x{N}x{K}", flush=True)
@@ -71,6 +73,7 @@ def test_gemm_workgroup_tiles(hq, cast, tile, M, N, K):
     out16 = fn(plan, *ops, out_dtype=torch.bfloat16)
     torch.cuda.synchronize()
     rel = float((out.double() - ref).norm() / ref.norm())
+    print(f"relative error {rel:.3g}", flush=True)
     # fp32 accumulation: int8 tile sums are exact and MXFP4 products too; each of
     # the K / tile (K / 64) additions rounds by 2^-24 of a running sum that the
     # result's size bounds on average.  The E4M3 matrix cores align the products
