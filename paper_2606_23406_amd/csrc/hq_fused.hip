@@ -825,11 +825,13 @@ __global__ __launch_bounds__(256) void hq_act_prep_kernel(hq_actprep_args A) {
   }
   if (A.tile > HQ_TILE) {
     // the remaining butterflies of a long tile, one stage at a time over the
-    // row: pair p of stage h is (j, j + h) with j = (p / h) 2h + p % h
-    for (int64_t h = HQ_TILE; h < A.tile; h <<= 1) {
+    // row: pair p of stage h, a power of two, is (j, j + h) with j = (p / h) 2h +
+    // p % h = p + (p & -h).  With 64-bit divisions by h 16 x 14336 to E4M3 at
+    // tile 512 took 18.7 us instead of 13.4, 4096 x 4096 28.5 instead of 20.7.
+    for (uint32_t h = HQ_TILE; h < (uint32_t)A.tile; h <<= 1) {
       __syncthreads();
-      for (int64_t p2 = tid; p2 < A.K / 2; p2 += 256) {
-        const int64_t j = (p2 / h) * 2 * h + p2 % h;
+      for (uint32_t p = (uint32_t)tid; p < (uint32_t)A.K / 2; p += 256) {
+        const uint32_t j = p + (p & (0u - h));
         const float a = ybuf[j], b = ybuf[j + h];
         ybuf[j] = a + b;
         ybuf[j + h] = a - b;
