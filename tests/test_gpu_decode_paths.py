@@ -37,8 +37,6 @@ def hq():
 @pytest.mark.parametrize("rows", [3, 4100])   # one sub-stream per wave, and four (a ragged last wave)
 def test_parse_paths(hq, lat, snr, rice_k, rows):
     cols = 512 if rows == 3 else 2048
-    if rows > 3 and lat not in (O.E8, O.D4):
-        pytest.skip("the four-per-wave launch shape at two lattices")
     P = PT.oracle_params(lat, snr, rht_seed=71, rice_k=rice_k)
     x = gauss(rows, cols, 500 + rows, 0.02, torch.bfloat16)
     check_roundtrip(hq, P, snr, x, f"parse paths lattice {lat} {snr} dB k={rice_k}")
