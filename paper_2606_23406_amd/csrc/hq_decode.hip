@@ -10,10 +10,11 @@
 namespace {
 
 // 16 output bytes that this kernel does not read again: past the caches, which
-// keep the payload.  A layer of seven E8@4 matrices 177.5 us with plain stores,
-// 148 so; 32768 x 1024 KV rows 52.7 and 50.8.  A product of 16 rows that reads the
-// matrix next finds less of it in the caches: with its decode, 14336 x 4096 takes
-// 67.3 and 73.1 us, 2048 x 4096 28.8 and 27.3.
+// keep the payload.  A layer of seven E8@4 matrices takes 176 us with plain stores
+// and 168 so (178 and 148 where the same streams are decoded again), 32768 x 1024
+// KV rows 50.8 and 48.9.  A product of 16 rows that reads the matrix next finds
+// less of it in the caches: with its decode, 14336 x 4096 takes 67 and 73 us,
+// 2048 x 4096 28.8 and 27.3.
 __device__ __forceinline__ void store_stream(void* p, uint4 v) {
   __builtin_nontemporal_store((v4u_t){v.x, v.y, v.z, v.w}, (v4u_t*)p);
 }

@@ -264,8 +264,8 @@ __device__ __forceinline__ void encode_substream(const hq_encode_args& A, const 
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i] = flip(x[i], sbits, i);
   }
-  // z <- S z, S^T read from global memory (a workgroup copy in LDS measured
-  // 3x slower on the one-sub-stream-per-wave appends)
+  // z <- S z, S^T read from global memory (a workgroup copy in LDS was tried only
+  // while LDS reads were misaligned, 64 cycles each: 3x slower then)
   if (KV && A.rotation == HQ_ROT_QJL) qjl_wave(A.qjlt, stage, lane, x);
   if (use_dither) {
     float u[8];

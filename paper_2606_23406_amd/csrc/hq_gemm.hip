@@ -288,8 +288,8 @@ __device__ __forceinline__ void gemm_tile_of(uint32_t id, uint32_t gm, uint32_t 
 // The product.  A wave walks its NA x NB blocks (a-major) once per stage:
 // block j's MFMAs (one chain over the stage's K) are issued between parts of
 // the previous block's rescale into the fp32 accumulators (an MFMA runs 32 or
-// 64 cycles and takes one issue slot, so the rescale's VALU work fits under
-// it), and each step's A fragment is replaced by the next block's as soon as
+// 64 cycles and takes one issue slot, so most of the rescale's VALU work runs
+// under it), and each step's A fragment is replaced by the next block's as soon as
 // its last MFMA is issued; scheduling barriers keep that order.  Before the
 // stage's last block every fragment of the stage is in registers: there the
 // wave waits for its own loads of the next stage, one workgroup barrier
@@ -297,14 +297,17 @@ __device__ __forceinline__ void gemm_tile_of(uint32_t id, uint32_t gm, uint32_t 
 // one's A rows), A's loads of stage t + R begin into this stage's slot, and
 // the next stage's first fragments are read under the last block's MFMAs.
 //
-// What bounds it: with every CU busy, power.  A round of 256 x 256 tiles takes
-// 1.43 us per stage (int8, tile 128) on 8 CUs and 2.4 us on 256, with or
-// without its loads' memory traffic; the MFMAs alone take 0.87 us on constant
-// and 1.24 us on random operands.  4096 x 14336 x 4096, random operands:
-// int8 288 us, E4M3 242 us, MXFP4 141 us, against 370, 318 and 230 us with 256
-// x 128 tiles whose eight waves alternated a load-and-rescale phase with an
-// MFMA phase (64 x 64 outputs a wave: half as many products per LDS byte, and
-// the two phases' times added up).
+// What bounds it: no one unit.  The matrix cores are busy 0.46 (int8), 0.52 (E4M3)
+// and 0.47 (MXFP4) of the SIMD cycles at 256 x 256; a stage's fragment reads and
+// row loads keep LDS for about as many cycles as its MFMAs take; and the rescale
+// under them still costs int8 a quarter (4096 x 14336 x 4096 at tile 512, one
+// rescale per four stages and 256 x 128 tiles: 256 us against 340).  With every CU busy
+// the clock falls too: a stage takes 1.43 us on 8 CUs and 2.4 us on 256 (int8, tile
+// 128), its MFMAs alone 0.87 us on constant and 1.24 us on random operands.  4096
+// x 14336 x 4096, random operands: int8 288 us, E4M3 242 us, MXFP4 141 us, against
+// 370, 318 and 230 us with 256 x 128 tiles whose eight waves alternated a load-and-
+// rescale phase with an MFMA phase (64 x 64 outputs a wave: half as many products
+// per LDS byte, and the two phases' times added up).
 template <class C>
 __device__ __forceinline__ void gemm_body(const hq_gemm_args& A) {
   using acc_t = typename C::acc_t;
