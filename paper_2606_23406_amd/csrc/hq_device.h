@@ -1099,7 +1099,9 @@ __device__ __forceinline__ float xor_sign(float v, uint32_t bit) {
 
 constexpr float kE8Tie = 1.0e-3f;  // band on the full-scale distance difference
 
-// x + carry-in / x - borrow-in, the carry a lane mask (bit l for lane l).
+// x + carry-in / x - borrow-in, the carry a lane mask (bit l for lane l) that
+// scalar logic made: straight from a vector compare it would need two wait
+// states, which the compiler does not keep before inline assembly.
 __device__ __forceinline__ int32_t add_lanemask(int32_t x, uint64_t m) {
   int32_t r;
   uint64_t co;

@@ -118,8 +118,8 @@ def test_gemm_assembly_reads_no_vector_registers():
 
 def test_scalar_operands_wait():
     """A vector instruction in inline assembly with a scalar register operand has the two wait states
-    in front that it needs behind a vector instruction that wrote the register; carry operands need
-    none."""
+    in front that it needs behind a vector instruction that wrote the register; those with a carry are
+    looked at below, as compiled."""
     seen = 0
     for path, body in asm_statements():
         ops = re.findall(r"\b(v_\w+)", body)
@@ -128,3 +128,50 @@ def test_scalar_operands_wait():
         seen += 1
         assert re.match(r'\s*"s_nop [1-9]', body), (path, body)
     assert seen > 0
+
+
+CARRY_PROBE = r"""
+#include "hq_device.h"
+__global__ __launch_bounds__(256) void probe(const float* w, int32_t* o) {
+  float v[8];
+  int32_t h[8], cb;
+  for (int j = 0; j < 8; ++j) v[j] = w[8 * threadIdx.x + j];
+  e8_nearest(v, h, cb);
+  for (int j = 0; j < 8; ++j) o[9 * threadIdx.x + j] = h[j];
+  o[9 * threadIdx.x + 8] = cb;
+}
+"""
+
+
+def test_carry_masks_come_from_scalar_logic(tmp_path):
+    """The lane masks that the E8 decision's inline assembly takes as carries are last written by scalar
+    instructions, or two wait states before."""
+    from paper_2606_23406_amd import build
+    src, s = tmp_path / "probe.hip", tmp_path / "probe.s"
+    src.write_text(CARRY_PROBE)
+    flags = [f for f in build.FLAGS if f not in ("-fPIC", "-Wall")]
+    subprocess.run([build.HIPCC] + flags + ["-w", "-I", CSRC, "-S", "--offload-device-only", "-o", str(s), str(src)],
+                   check=True, timeout=120)
+    body = re.search(r"\n_Z\d+probe\w*:(.*?)s_endpgm", s.read_text(), re.S).group(1)
+
+    def pairs(t):
+        return {i for lo, hi in re.findall(r"\bs\[(\d+):(\d+)\]", t) for i in (int(lo), int(hi))} | (
+            {"vcc"} if re.search(r"\bvcc\b", t) else set())
+    lines = [t for t in (line.split(";")[0].strip() for line in body.split("\n")) if t and t[0] != "."]
+    seen = 0
+    for n, t in enumerate(lines):
+        if not re.match(r"v_(addc|subb)_co_u32", t):
+            continue
+        mask, states = pairs(t.split(",")[-1]), 0
+        assert mask
+        seen += 1
+        for u in reversed(lines[:n]):
+            if u.startswith("s_nop"):
+                states += int(u.split()[1]) + 1
+                continue
+            written = pairs(u.split(",")[1] if re.match(r"v_\w+_co_", u) else u.split(",")[0])
+            if written & mask:
+                assert u.startswith("s_") or states >= 2, (u, t)
+                break
+            states += 1
+    assert seen >= 16
